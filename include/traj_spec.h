@@ -394,7 +394,7 @@ traj_status traj_refresh_layer(void* x, const traj_layer_weights* weights, const
  * Limits: K and N multiples of 8 (>= 8), M >= 0 (0 = no-op) and below 2^31 - 256, pointers
  * 16-byte aligned; y must not overlap x or w.  The kernels address operands through 32-bit
  * buffer offsets: K <= 2^22 and N <= 2^24, else TRAJ_E_UNSUPPORTED.  Nothing is allocated.
- * workspace (optional, may be NULL): shapes whose 128 x 128 tiles leave CUs idle (few rows:
+ * workspace (optional, may be NULL): shapes whose tiles leave CUs idle (few rows:
  * one or a few sequences' drafts) split K over several workgroups when given at least
  * traj_linear_workspace_size(M, K, N) bytes, 16-byte aligned, for the fp32 partial products
  * (a size of 0 means the shape is never split); with NULL the call runs unsplit.  A non-NULL

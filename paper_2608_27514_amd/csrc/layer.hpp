@@ -1,13 +1,12 @@
 // One verification layer around the trajectory-masked attention (a pre-norm decoder layer of
 // the 8B-shaped diffusion LMs the method runs on): the elementwise kernels between the
-// library GEMMs.  All activations are bf16 in HBM, arithmetic in fp32.
+// library GEMMs (SwiGLU is part of the gate / up projection's epilogue).  All activations are bf16 in HBM, arithmetic in fp32.
 //   rmsnorm_kernel     out = x / sqrt(mean(x^2) + eps) * w            (one workgroup per token)
 //   rope_split_kernel  [q | k | v] rows of the QKV projection -> q, k_draft, v_draft in the
 //                      attention's layouts, rotary position embedding on q and k (pairs d and
 //                      d + D/2, angle = pos * theta^(-2d/D)); token p of every draft of a block
 //                      sits at position pos0[b] + p (the drafts are alternative states of the
 //                      same block)
-//   swiglu_kernel      act = silu(gate) * up from the [gate | up] rows of the gate/up projection
 //   cache_gather_kernel  the dual-cache refresh's copy of the rotated K / V rows outside the
 //                      current block into the prefix | suffix cache
 #pragma once
@@ -115,30 +114,6 @@ __global__ __launch_bounds__(kLayerThreads) void rope_split_kernel(const uint16_
     uint16_t* vdst = vd + (int64_t)t * Hkv * D;
     for (int i = threadIdx.x; i < Hkv * D / 8; i += kLayerThreads)
         *reinterpret_cast<u32x4_t*>(vdst + 8 * i) = *reinterpret_cast<const u32x4_t*>(vsrc + 8 * i);
-}
-
-// gu: [T, 2 I] rows [gate | up]; act: [T, I].  Grid-stride over the T * I / 8 chunks of
-// 8 elements (I % 8 == 0).
-__global__ __launch_bounds__(kLayerThreads) void swiglu_kernel(const uint16_t* __restrict__ gu,
-                                                               uint16_t* __restrict__ act, int64_t T, int I) {
-    const int cpr = I / 8;  // chunks per row
-    const int64_t total = T * cpr;
-    for (int64_t q = (int64_t)blockIdx.x * kLayerThreads + threadIdx.x; q < total;
-         q += (int64_t)gridDim.x * kLayerThreads) {
-        const int64_t t = q / cpr;
-        const int i = (int)(q - t * cpr);
-        const u32x4_t g = *reinterpret_cast<const u32x4_t*>(gu + t * 2 * I + 8 * i);
-        const u32x4_t u = *reinterpret_cast<const u32x4_t*>(gu + t * 2 * I + I + 8 * i);
-        u32x4_t o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const float g0 = bf16_lo(g[e]), g1 = bf16_hi(g[e]);
-            const float a = g0 / (1.0f + __expf(-g0)) * bf16_lo(u[e]);
-            const float c = g1 / (1.0f + __expf(-g1)) * bf16_hi(u[e]);
-            o[e] = (uint32_t)f2bf(a) | ((uint32_t)f2bf(c) << 16);
-        }
-        *reinterpret_cast<u32x4_t*>(act + t * I + 8 * i) = o;
-    }
 }
 
 // Dual-cache refresh: the rotated K and V rows of every position outside the current block go

@@ -162,86 +162,140 @@ traj_status launch_topk(const void* logits, const traj_logits_shape* sh, int k, 
 }
 
 // ------------------------------------------------------------------ verification layer
-// Split-K for grids of 128 x 128 tiles that leave CUs idle: up to kGemmMaxSplits k ranges of
-// at least kGemmMinSplitK each, so that tiles x splits stays within one workgroup per CU.
+// Tilings of the projection GEMM with the figures its plan is made from, measured on an MI355X:
+// the microseconds one 64-wide k step takes with a workgroup on every CU (one and two rounds of
+// 256 workgroups over K = 4096 and 12288), the rate in TB/s at which the weights stream when they
+// bound the call (wider tiles read longer row segments: LM head of 64 rows 240 / 194 / 176 us with
+// 64 / 128 / 256 columns), and the microseconds to fill and drain the stage ring.  Large tiles do
+// more arithmetic per step and byte, small ones fill the chip where M x N is small.
+struct GemmTiling {
+    int bm, bn, threads;
+    float step_us, stream, fill_us;
+    void (*kernel[4])(GemmParams);  // by GemmEpilogue
+};
+#define TRAJ_RING_TILING(BM, BN, WM, WN, S, KC, NT, STEP, STREAM, FILL)                                             \
+    {BM, BN, WM * WN * 64, STEP, STREAM, FILL,                                                                      \
+     {gemm_ring_kernel<BM, BN, WM, WN, S, KC, NT, kEpiStore>, gemm_ring_kernel<BM, BN, WM, WN, S, KC, NT, kEpiAccumulate>, \
+      gemm_ring_kernel<BM, BN, WM, WN, S, KC, NT, kEpiPartial>, gemm_ring_kernel<BM, BN, WM, WN, S, KC, NT, kEpiSwiglu>}}
+const GemmTiling kGemmTilings[] = {
+    TRAJ_RING_TILING(64, 64, 2, 2, 9, 4, false, 0.30f, 4.0f, 2.0f),
+    TRAJ_RING_TILING(64, 128, 2, 2, 3, 2, true, 0.42f, 5.5f, 4.0f),
+    TRAJ_RING_TILING(64, 256, 1, 4, 4, 1, true, 0.85f, 5.7f, 4.0f),
+    TRAJ_RING_TILING(128, 128, 2, 2, 4, 1, false, 0.55f, 5.0f, 4.0f),
+    TRAJ_RING_TILING(256, 96, 4, 1, 3, 1, false, 0.82f, 5.0f, 4.0f),
+    TRAJ_RING_TILING(256, 128, 4, 2, 3, 1, true, 0.90f, 5.4f, 4.0f),
+    TRAJ_RING_TILING(128, 192, 2, 2, 4, 1, false, 0.86f, 5.4f, 4.0f),
+    TRAJ_RING_TILING(192, 128, 2, 2, 4, 1, false, 0.74f, 5.0f, 4.0f),
+    TRAJ_RING_TILING(128, 256, 2, 4, 3, 1, false, 0.90f, 5.4f, 4.0f),
+    TRAJ_RING_TILING(192, 192, 2, 2, 3, 1, false, 1.03f, 5.4f, 4.0f),
+    {kG2BM, kG2BN, kG2Threads, 1.62f, 5.4f, 4.0f,
+     {gemm_tile256_kernel<kEpiStore>, gemm_tile256_kernel<kEpiAccumulate>, nullptr, gemm_tile256_kernel<kEpiSwiglu>}},
+};
+#undef TRAJ_RING_TILING
+
+constexpr int kGemmCus = 256;           // workgroups the chip runs at a time
 constexpr int kGemmMaxSplits = 8;
 constexpr int64_t kGemmMinSplitK = 512;
+// SwiGLU goes into the GEMM's own epilogue from this many rows on: there the projection is bound
+// by the matrix cores and the gate / up values' round trip through memory costs as much as it
+// saves (768 rows: 147 us against 134 + 11) or more (32768 rows).  With fewer rows the weights'
+// streaming bounds it and the two half-width column segments per row cost more than the separate
+// launch (224 rows: 67 against 57 + 5 us; 64 rows: 48 against 42 + 5).
+constexpr int64_t kSwigluFuseMinRows = 512;
 
-struct GemmSplit {
-    int splits;
-    int k_split;
+struct GemmPlan {
+    const GemmTiling* tiling;
+    int64_t tiles_m, tiles_n;
+    int splits, k_split;
 };
 
-GemmSplit plan_split(int64_t M, int64_t N, int64_t K) {
-    const int64_t big = ((M + kG2BM - 1) / kG2BM) * ((N + kG2BN - 1) / kG2BN);
-    const int64_t tiles = ((M + kGemmBM - 1) / kGemmBM) * ((N + kGemmBN - 1) / kGemmBN);
-    if (big >= kGemmBigGridMin || tiles >= 256) return {1, 0};
-    int64_t S = std::min<int64_t>(256 / tiles, kGemmMaxSplits);
-    while (S > 1 && K / S < kGemmMinSplitK) --S;
-    if (S <= 1) return {1, 0};
-    const int64_t k_split = ((K + S - 1) / S + kGemmBK - 1) / kGemmBK * kGemmBK;
-    return {(int)((K + k_split - 1) / k_split), (int)k_split};
+// The tiling and K split with the least estimated time: rounds of workgroups over the CUs times
+// their steps, but at least the weights' streaming time, and for a split the second launch and its
+// partial products' traffic (written and read: 9 TB/s).  A split's reduction applies SwiGLU at no
+// cost; without one it is a launch of its own below kSwigluFuseMinRows.  Within a few percent of the
+// best measured tiling on 32 .. 2048 rows x the 8B projections.
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool swiglu, bool may_split) {
+    GemmPlan best{};
+    double best_us = 0.0;
+    const int64_t steps = (K + kGemmBK - 1) / kGemmBK;
+    for (const GemmTiling& g : kGemmTilings) {
+        const int64_t tm = (M + g.bm - 1) / g.bm, tn = (N + g.bn - 1) / g.bn;
+        const double stream_us = (double)K * (double)N * 2e-6 / g.stream;
+        for (int s = 1; s <= kGemmMaxSplits; ++s) {
+            if (s > 1 && (!may_split || g.kernel[kEpiPartial] == nullptr || K / s < kGemmMinSplitK || tm * tn * s > kGemmCus)) break;
+            const int64_t split_steps = (steps + s - 1) / s;
+            if ((steps + split_steps - 1) / split_steps != s) continue;  // the same as a smaller s
+            const double rounds = (double)((tm * tn * s + kGemmCus - 1) / kGemmCus);
+            double us = std::max(rounds * (double)split_steps * g.step_us, stream_us) + g.fill_us;
+            if (s > 1) us += 2.0 + 0.4 * s + (double)s * (double)M * (double)N * 8.0 / 9e6;
+            if (s == 1 && swiglu && M < kSwigluFuseMinRows) us += 6.0;
+            if (best.tiling == nullptr || us < best_us) {
+                best = GemmPlan{&g, tm, tn, s, s > 1 ? (int)(split_steps * kGemmBK) : 0};
+                best_us = us;
+            }
+        }
+    }
+    return best;
 }
+
+bool gemm_sizes_ok(int64_t M, int64_t N, int64_t K) { return M >= 1 && N >= 8 && K >= 8 && K <= kGemmMaxK && N <= kGemmMaxN; }
 
 // fp32 partial products of a split GEMM (0 when the shape is not split)
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
-    if (M < 1 || N < 8 || K < 8 || K > kGemmMaxK || N > kGemmMaxN) return 0;
-    const GemmSplit sp = plan_split(M, N, K);
-    return sp.splits > 1 ? (size_t)sp.splits * (size_t)M * (size_t)N * sizeof(float) : 0;
+    if (!gemm_sizes_ok(M, N, K)) return 0;
+    const int splits = plan_gemm(M, N, K, false, true).splits;
+    return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(float) : 0;
 }
 
-// D[M,N] = A[M,K] W[K,N] (+ D when accumulate), bf16 row-major, fp32 accumulation.  `ws` (may
-// be null) holds the split-K partials when the shape is split and it is large enough.
-traj_status gemm(const uint16_t* A, const uint16_t* W, uint16_t* D, int64_t M, int64_t N, int64_t K, bool accumulate,
+// Scratch of the gate / up projection with SwiGLU: the partial products, or the [M, N] gate / up
+// values where SwiGLU is a launch of its own.
+size_t gemm_swiglu_workspace_bytes(int64_t M, int64_t N, int64_t K) {
+    if (!gemm_sizes_ok(M, N, K)) return 0;
+    const int splits = plan_gemm(M, N, K, true, true).splits;
+    if (splits > 1) return (size_t)splits * (size_t)M * (size_t)N * sizeof(float);
+    return M < kSwigluFuseMinRows ? (size_t)M * (size_t)N * sizeof(uint16_t) : 0;
+}
+
+// D[M,N] = A[M,K] W[K,N] (+ D with kEpiAccumulate), or with kEpiSwiglu D[M,N/2] = silu(gate) * up
+// of the product's [gate | up] columns; bf16 row-major, fp32 accumulation.  `ws` holds the split-K
+// partials (may be null or too small except for SwiGLU: the shape then runs unsplit).
+traj_status gemm(const uint16_t* A, const uint16_t* W, uint16_t* D, int64_t M, int64_t N, int64_t K, GemmEpilogue epi,
                  void* ws, size_t ws_bytes, hipStream_t st) {
     if (M < 1 || N < 8 || K < 8 || N % 8 != 0 || K % 8 != 0) return TRAJ_E_SHAPE;
     if (M > INT_MAX - kG2BM) return TRAJ_E_SHAPE;
     if (K > kGemmMaxK || N > kGemmMaxN) return TRAJ_E_UNSUPPORTED;  // 32-bit buffer offsets
     if (!aligned16(A) || !aligned16(W) || !aligned16(D)) return TRAJ_E_SHAPE;
-    // 256 x 256 tiles when they alone fill the chip, else 128 x 128 tiles with the stage ring
-    const int64_t big_m = (M + kG2BM - 1) / kG2BM, big_n = (N + kG2BN - 1) / kG2BN;
-    if (big_m * big_n >= kGemmBigGridMin) {
-        const GemmParams p{A, W, D, (int)M, (int)N, (int)K, (int)big_m, (int)big_n, nullptr, 0};
-        const dim3 grid((unsigned)(big_m * big_n));
-        if (accumulate)
-            hipLaunchKernelGGL((gemm_tile256_kernel<true>), grid, dim3(kG2Threads), 0, st, p);
-        else
-            hipLaunchKernelGGL((gemm_tile256_kernel<false>), grid, dim3(kG2Threads), 0, st, p);
-        return launched();
+    const bool swiglu = epi == kEpiSwiglu;
+    GemmPlan g = plan_gemm(M, N, K, swiglu, true);
+    if (g.splits > 1 &&
+        (ws == nullptr || ws_bytes < (size_t)g.splits * (size_t)M * (size_t)N * sizeof(float) || !aligned16(ws)))
+        g = plan_gemm(M, N, K, swiglu, false);
+    const bool apart = swiglu && g.splits == 1 && M < kSwigluFuseMinRows;  // SwiGLU as its own launch
+    if (apart && (ws == nullptr || ws_bytes < (size_t)M * (size_t)N * sizeof(uint16_t) || !aligned16(ws))) return TRAJ_E_WORKSPACE;
+    const dim3 grid((unsigned)(g.tiles_m * g.tiles_n), (unsigned)g.splits);
+    const GemmParams p{A, W, apart ? static_cast<uint16_t*>(ws) : D, (int)M, (int)N, (int)K, (int)g.tiles_m, (int)g.tiles_n,
+                       g.splits > 1 ? static_cast<float*>(ws) : nullptr, g.k_split};
+    hipLaunchKernelGGL(g.tiling->kernel[g.splits > 1 ? kEpiPartial : apart ? kEpiStore : epi], grid, dim3(g.tiling->threads), 0,
+                       st, p);
+    const traj_status rs = launched();
+    if (rs != TRAJ_OK || (g.splits == 1 && !apart)) return rs;
+    const int64_t chunks = M * (swiglu ? N / 2 : N) / 8;
+    const dim3 rgrid((unsigned)std::min<int64_t>((chunks + 255) / 256, 4096));
+    if (apart) {
+        hipLaunchKernelGGL(swiglu_kernel, rgrid, dim3(256), 0, st, static_cast<const uint16_t*>(ws), D, (int)M, (int)N);
+    } else {
+        auto reduce = swiglu                  ? gemm_split_reduce_kernel<kEpiSwiglu>
+                      : epi == kEpiAccumulate ? gemm_split_reduce_kernel<kEpiAccumulate>
+                                              : gemm_split_reduce_kernel<kEpiStore>;
+        hipLaunchKernelGGL(reduce, rgrid, dim3(256), 0, st, static_cast<const float*>(ws), g.splits, D, (int)M, (int)N);
     }
-    const int64_t tiles_m = (M + kGemmBM - 1) / kGemmBM, tiles_n = (N + kGemmBN - 1) / kGemmBN;
-    const dim3 grid((unsigned)(tiles_m * tiles_n));  // fewer than 4 x 256 tiles
-    const GemmSplit sp = plan_split(M, N, K);
-    const size_t need = gemm_workspace_bytes(M, N, K);
-    if (sp.splits > 1 && ws != nullptr && ws_bytes >= need && aligned16(ws)) {
-        const GemmParams p{A, W, D, (int)M, (int)N, (int)K, (int)tiles_m, (int)tiles_n, static_cast<float*>(ws),
-                           sp.k_split};
-        hipLaunchKernelGGL((gemm_ring128_kernel<false, true>), dim3(grid.x, (unsigned)sp.splits), dim3(kGemmThreads),
-                           0, st, p);
-        traj_status rs = launched();
-        if (rs != TRAJ_OK) return rs;
-        const int64_t chunks = M * N / 8;
-        const dim3 rgrid((unsigned)std::min<int64_t>((chunks + 255) / 256, 4096));
-        if (accumulate)
-            hipLaunchKernelGGL((gemm_split_reduce_kernel<true>), rgrid, dim3(256), 0, st,
-                               static_cast<const float*>(ws), sp.splits, D, (int)M, (int)N);
-        else
-            hipLaunchKernelGGL((gemm_split_reduce_kernel<false>), rgrid, dim3(256), 0, st,
-                               static_cast<const float*>(ws), sp.splits, D, (int)M, (int)N);
-        return launched();
-    }
-    const GemmParams p{A, W, D, (int)M, (int)N, (int)K, (int)tiles_m, (int)tiles_n, nullptr, 0};
-    if (accumulate)
-        hipLaunchKernelGGL((gemm_ring128_kernel<true, false>), grid, dim3(kGemmThreads), 0, st, p);
-    else
-        hipLaunchKernelGGL((gemm_ring128_kernel<false, false>), grid, dim3(kGemmThreads), 0, st, p);
     return launched();
 }
 
 size_t align256(size_t n) { return (n + 255) / 256 * 256; }
 
 struct LayerPlan {
-    size_t xn, qkv, q, kd, vd, a, gu, act, split, split_bytes, total;
+    size_t xn, qkv, q, kd, vd, a, act, split, split_bytes, total;
 };
 
 LayerPlan plan_layer(const traj_attn_shape* sh, const traj_layer_dims* dm) {
@@ -259,11 +313,10 @@ LayerPlan plan_layer(const traj_attn_shape* sh, const traj_layer_dims* dm) {
     p.kd = take(T * (size_t)sh->Hkv * sh->D * 2);
     p.vd = take(T * (size_t)sh->Hkv * sh->D * 2);
     p.a = take(T * (size_t)sh->Hq * sh->D * 2);
-    p.gu = take(T * 2 * (size_t)dm->inter * 2);
     p.act = take(T * (size_t)dm->inter * 2);
     const int64_t hid = dm->hidden, qkv_w = (int64_t)(sh->Hq + 2 * sh->Hkv) * sh->D;
     p.split_bytes = std::max(std::max(gemm_workspace_bytes(T, qkv_w, hid), gemm_workspace_bytes(T, hid, (int64_t)sh->Hq * sh->D)),
-                             std::max(gemm_workspace_bytes(T, 2 * (int64_t)dm->inter, hid),
+                             std::max(gemm_swiglu_workspace_bytes(T, 2 * (int64_t)dm->inter, hid),
                                       gemm_workspace_bytes(T, hid, dm->inter)));
     p.split = take(p.split_bytes);
     p.total = off;
@@ -351,7 +404,7 @@ traj_status run_layer(uint16_t* xs, const traj_layer_weights* w, const traj_laye
     hipLaunchKernelGGL(rmsnorm_kernel, dim3((unsigned)T), dim3(kLayerThreads), 0, s, xs,
                        static_cast<const uint16_t*>(w->attn_norm), buf(plan.xn), hidden, dims->rms_eps);
     if ((st = launched()) != TRAJ_OK) return st;
-    if ((st = gemm(buf(plan.xn), static_cast<const uint16_t*>(w->w_qkv), buf(plan.qkv), T, qkv_w, hidden, false, split,
+    if ((st = gemm(buf(plan.xn), static_cast<const uint16_t*>(w->w_qkv), buf(plan.qkv), T, qkv_w, hidden, kEpiStore, split,
                    split_bytes, s)) != TRAJ_OK)
         return st;
     hipLaunchKernelGGL(rope_split_kernel, dim3((unsigned)T), dim3(kLayerThreads), 0, s, buf(plan.qkv), pos0,
@@ -359,21 +412,17 @@ traj_status run_layer(uint16_t* xs, const traj_layer_weights* w, const traj_laye
                        std::log2(dims->rope_theta));
     if ((st = launched()) != TRAJ_OK) return st;
     if ((st = attend(buf(plan.q), buf(plan.kd), buf(plan.vd), buf(plan.a))) != TRAJ_OK) return st;
-    if ((st = gemm(buf(plan.a), static_cast<const uint16_t*>(w->w_o), xs, T, hidden, (int64_t)Hq * D, true, split,
+    if ((st = gemm(buf(plan.a), static_cast<const uint16_t*>(w->w_o), xs, T, hidden, (int64_t)Hq * D, kEpiAccumulate, split,
                    split_bytes, s)) != TRAJ_OK)
         return st;
     // MLP block
     hipLaunchKernelGGL(rmsnorm_kernel, dim3((unsigned)T), dim3(kLayerThreads), 0, s, xs,
                        static_cast<const uint16_t*>(w->mlp_norm), buf(plan.xn), hidden, dims->rms_eps);
     if ((st = launched()) != TRAJ_OK) return st;
-    if ((st = gemm(buf(plan.xn), static_cast<const uint16_t*>(w->w_gate_up), buf(plan.gu), T, 2 * (int64_t)inter, hidden,
-                   false, split, split_bytes, s)) != TRAJ_OK)
+    if ((st = gemm(buf(plan.xn), static_cast<const uint16_t*>(w->w_gate_up), buf(plan.act), T, 2 * (int64_t)inter, hidden,
+                   kEpiSwiglu, split, split_bytes, s)) != TRAJ_OK)
         return st;
-    const int64_t chunks = T * (inter / 8);
-    hipLaunchKernelGGL(swiglu_kernel, dim3((unsigned)std::min<int64_t>((chunks + kLayerThreads - 1) / kLayerThreads, 16384)),
-                       dim3(kLayerThreads), 0, s, buf(plan.gu), buf(plan.act), T, inter);
-    if ((st = launched()) != TRAJ_OK) return st;
-    return gemm(buf(plan.act), static_cast<const uint16_t*>(w->w_down), xs, T, hidden, inter, true, split, split_bytes, s);
+    return gemm(buf(plan.act), static_cast<const uint16_t*>(w->w_down), xs, T, hidden, inter, kEpiAccumulate, split, split_bytes, s);
 }
 
 }  // namespace
@@ -672,7 +721,7 @@ traj_status traj_linear(const void* x, const void* w, void* y, int64_t M, int64_
     if (workspace != nullptr && (workspace_bytes < gemm_workspace_bytes(M, N, K) || !aligned16(workspace)))
         return TRAJ_E_WORKSPACE;
     return gemm(static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w), static_cast<uint16_t*>(y), M, N, K,
-                accumulate != 0, workspace, workspace_bytes, as_stream(stream));
+                accumulate != 0 ? kEpiAccumulate : kEpiStore, workspace, workspace_bytes, as_stream(stream));
 }
 
 const char* traj_status_string(int32_t status) {

@@ -140,6 +140,35 @@ def test_linear_full_size_sampled_rows(M, K, N, acc):
     assert (np.abs(got - ref) <= _linear_bound(a_s, w_h, y_s, ref)).all()
 
 
+@pytest.mark.parametrize("M,K,N", [
+    # every tiling of the GEMM's plan, with ragged rows, columns and k: unsplit ...
+    (16, 200, 72), (66, 1096, 8216), (130, 328, 11120), (580, 200, 8312), (521, 200, 11232), (321, 200, 11240),
+    (643, 200, 10912), (385, 200, 11144), (769, 200, 6936), (968, 200, 11088), (64, 512, 33000),
+    # ... and split over k, the last range ragged
+    (16, 1544, 72), (68, 1544, 8296), (2053, 2056, 904), (261, 2056, 6616), (129, 2056, 5472), (4129, 2056, 392),
+    (193, 2056, 8344),
+])
+@pytest.mark.parametrize("acc", [False, True])
+def test_linear_each_tiling(M, K, N, acc):
+    """Against the product in float64 with the bound above; the zeros past the last row, column and
+    k come from out-of-range loads, so neighbouring memory holds large values."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M * 7 + K + N)
+    pad = 4096
+    xb = torch.full((M * K + pad,), 1e30, device="cuda", dtype=torch.bfloat16)
+    wb = torch.full((K * N + pad,), 1e30, device="cuda", dtype=torch.bfloat16)
+    x, w = xb[:M * K].view(M, K), wb[:K * N].view(K, N)
+    x.copy_(torch.randn(M, K, device="cuda", generator=g))
+    w.copy_(torch.randn(K, N, device="cuda", generator=g) * K ** -0.5)
+    y0 = torch.randn(M, N, device="cuda", generator=g).to(torch.bfloat16) if acc else None
+    out = tsp.linear(x, w, y=y0.clone() if acc else None, accumulate=acc)
+    x64, w64 = x.double(), w.double()
+    ref, mag = x64 @ w64, x64.abs() @ w64.abs()
+    if acc:
+        ref, mag = ref + y0.double(), mag + y0.double().abs()
+    assert ((out.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2.0 ** -15 * mag).all()
+
+
 def test_linear_split_and_unsplit_agree():
     """A shape that splits K runs unsplit without a workspace; both are within the bound of the
     exact product, and the split path is the one taken with a workspace."""
