@@ -128,6 +128,24 @@ def test_short_batch_launches_ragged_vocab(rows, V):
         _check(x.to(dt).cuda(), 3, label=f"rows={rows} V={V} {dt}")
 
 
+# Rows that start anywhere inside a 16-byte vector: an odd stride moves the start from row to row
+# through every offset, under each launch shape (split rows, 8, 4 and 1 waves per row); V = 1 .. 5 is
+# shorter than the run up to the first aligned vector.
+@pytest.mark.parametrize("rows,V", [(40, 1), (40, 5), (40, 12301), (130, 16391), (130, 32999), (520, 4099),
+                                    (520, 20011), (4100, 1031), (4100, 9), (3, 126463)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_rows_at_every_alignment(rows, V, dtype):
+    rng = np.random.default_rng(rows + V)
+    stride = V + 2 if V % 2 else V + 1
+    x = torch.full((rows * stride + 1,), 1e30, dtype=dtype)  # the padding between rows would win
+    x = x.as_strided((rows, V), (stride, 1), 1)
+    x.copy_(torch.from_numpy(rng.standard_normal((rows, V)).astype(np.float32)))
+    base = torch.empty(rows * stride + 1, dtype=dtype, device="cuda")
+    base.copy_(x.as_strided((rows * stride + 1,), (1,), 0))
+    sample = np.unique(np.concatenate([np.arange(min(rows, 40)), rng.choice(rows, size=min(rows, 60), replace=False)]))
+    _check(base.as_strided((rows, V), (stride, 1), 1), min(3, V), rows=sample, label=f"rows={rows} V={V} {dtype}")
+
+
 def test_negative_infinity_entries():
     x = torch.full((4, 300), -float("inf"))
     x[:, 5] = 1.0
