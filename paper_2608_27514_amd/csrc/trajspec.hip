@@ -76,6 +76,11 @@ int device_cu_count() {
     return cus;
 }
 
+// 16-row grids with a longer cache than this run two key groups per workgroup (two waves per SIMD,
+// half the chain of steps each): 736 keys 16.9 -> 14.9 us, 4096 keys 54.5 -> 45.3 (8 drafts x 32
+// heads), 256 keys 10.6 -> 10.2; at 192 keys and below the merge costs what the steps save.
+constexpr int kAttnSplitKeysMin = 192;
+
 // p describes the 32-row launch (4 waves x 32 rows per workgroup).  A grid that still has at
 // most one workgroup per CU with 16-row waves (4 waves x 16 rows per workgroup, twice the
 // workgroups) runs that way: each wave's chain of steps is half as long.  Larger grids keep
@@ -88,7 +93,10 @@ traj_status launch_attn(AttnParams p, hipStream_t st) {
     if (nwg16 <= device_cu_count()) {
         p.wg_per_group = wg16;
         p.num_wg = (int)nwg16;
-        hipLaunchKernelGGL(verify_attn16_kernel<D>, dim3(p.num_wg), dim3(kAttnThreads), 0, st, p);
+        if (p.S > kAttnSplitKeysMin)
+            hipLaunchKernelGGL((verify_attn16_kernel<D, 2>), dim3(p.num_wg), dim3(2 * kAttnThreads), 0, st, p);
+        else
+            hipLaunchKernelGGL((verify_attn16_kernel<D, 1>), dim3(p.num_wg), dim3(kAttnThreads), 0, st, p);
     } else {
         hipLaunchKernelGGL(verify_attn_kernel<D>, dim3(p.num_wg), dim3(kAttnThreads), 0, st, p);
     }

@@ -22,6 +22,10 @@
 //   takes the same keys through two transposing LDS reads (rows 4 q .. + 3 and 16 + 4 q .. + 3).
 //   O^T in lane l: head dims 16 db + 4 q .. + 3 of query l % 16 (one 8-byte store per block db).
 //
+// Key groups: such a grid leaves SIMDs with one wave or none and a wave's time is its chain of cache
+// steps (~1600 cycles each for 512 of MFMA), so longer caches are shared by two groups of 4 waves
+// in one workgroup, each with its own keys, stage buffers and running state, merged at the end.
+//
 // Phases, stage layout, lazy online softmax, ancestor masks and the draft tile walk are those of
 // the 32-row kernel (verify_attn.hpp).
 #pragma once
@@ -260,16 +264,22 @@ __device__ __forceinline__ void draft_tile16(const DraftArgs& a, int k0, int q, 
         o[db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v_frag16<D>(vw, ln, db), pf, o[db], 0, 0, 0);
 }
 
-template <int D>
-__global__ __launch_bounds__(kAttnThreads, 2) void verify_attn16_kernel(AttnParams P) {
+// KG key groups of 4 waves each: group kg takes its share of the cache steps (a range of keys of its
+// own, through stage buffers of its own) and every KG-th draft tile; the groups' outputs, references
+// and sums are merged through LDS at the end.
+template <int D, int KG>
+__global__ __launch_bounds__(kAttnThreads* KG, 2 / KG) void verify_attn16_kernel(AttnParams P) {
     using G = AttnGeom<D, 16>;
-    __shared__ __attribute__((aligned(1024))) uint16_t buf0[G::kStageElems];
-    __shared__ __attribute__((aligned(1024))) uint16_t buf1[G::kStageElems];
+    __shared__ __attribute__((aligned(1024))) uint16_t buf0_all[KG * G::kStageElems];
+    __shared__ __attribute__((aligned(1024))) uint16_t buf1_all[KG * G::kStageElems];
     __shared__ uint64_t anc[64];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = wave_all % kAttnWaves, kg = wave_all / kAttnWaves;  // wave within its key group
+    uint16_t* buf0 = buf0_all + kg * G::kStageElems;
+    uint16_t* buf1 = buf1_all + kg * G::kStageElems;
     const int q = lane >> 4;  // lane group: keys 4 q .. 4 q + 3 of each 16-key block
 
     const int lid = xcd_logical_id(blockIdx.x, P.num_wg);
@@ -277,12 +287,12 @@ __global__ __launch_bounds__(kAttnThreads, 2) void verify_attn16_kernel(AttnPara
     const int bg = lid / P.wg_per_group;
     const int g = bg % P.Hkv;
     const int b = bg / P.Hkv;
-    const int N = P.N, L = P.L, S = P.S;
+    const int N = P.N, L = P.L;
     const float c = P.scale_log2;
     const float thr = kLazyLog2 / c;
 
-    const int pj = (P.parent != nullptr && wave == 0 && lane < N) ? P.parent[(int64_t)b * N + lane] : -1;
-    const uint64_t peer_bits = (P.peers != nullptr && wave == 0 && lane < N) ? P.peers[(int64_t)b * N + lane] : 0ull;
+    const int pj = (P.parent != nullptr && wave_all == 0 && lane < N) ? P.parent[(int64_t)b * N + lane] : -1;
+    const uint64_t peer_bits = (P.peers != nullptr && wave_all == 0 && lane < N) ? P.peers[(int64_t)b * N + lane] : 0ull;
 
     // This lane's query row (lanes l, l^16, l^32, l^48 share a row).
     const int row = (wg_in_group * kAttnWaves + wave) * 16 + (lane & 15);
@@ -330,14 +340,20 @@ __global__ __launch_bounds__(kAttnThreads, 2) void verify_attn16_kernel(AttnPara
     SoftState st = {kNegInf, 0.f, kNegInf, 0.f};
 
     // ---------------- phase 1: cache keys ----------------
+    // this group's keys: steps [kg per_group, (kg + 1) per_group) of the cache
+    const int steps_all = (P.S + kAttnTile - 1) / kAttnTile;
+    const int steps_max = (steps_all + KG - 1) / KG;
+    const int key_first = min(kg * steps_max * kAttnTile, P.S);
+    const int S = min(steps_max * kAttnTile, P.S - key_first);
     CacheArgs ca;
     {
-        const uint16_t* kc_base = P.kc + ((int64_t)b * S * P.Hkv + g) * D;
-        const uint16_t* vc_base = P.vc + ((int64_t)b * S * P.Hkv + g) * D;
-        const int64_t total = (int64_t)P.B * S * P.Hkv * D * 2;
-        const int64_t start = ((int64_t)b * S * P.Hkv + g) * D * 2;
+        const int64_t first = (((int64_t)b * P.S + key_first) * P.Hkv + g) * D;
+        const uint16_t* kc_base = P.kc + first;
+        const uint16_t* vc_base = P.vc + first;
+        const int64_t total = (int64_t)P.B * P.S * P.Hkv * D * 2;
+        const int64_t start = first * 2;
         const int64_t rem = total - start;
-        const int nrec = rem > 0x7FFFFFFF ? 0x7FFFFFFF : (int)rem;
+        const int nrec = rem > 0x7FFFFFFF ? 0x7FFFFFFF : rem < 0 ? 0 : (int)rem;
         ca.krs = __builtin_amdgcn_make_buffer_rsrc((void*)kc_base, (short)0, nrec, kBufferFlags);
         ca.vrs = __builtin_amdgcn_make_buffer_rsrc((void*)vc_base, (short)0, nrec, kBufferFlags);
     }
@@ -363,7 +379,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void verify_attn16_kernel(AttnPara
             stage_dma<D, true, 16>(ca.krs, ca.vrs, kv_stride, 0, S, wave, ln, buf0);
         }
     }
-    if (wave == 0) {
+    if (wave_all == 0) {
         uint64_t msk = 1ull << lane;
         int j = pj, prev = lane;
         bool live = lane < N;
@@ -384,9 +400,9 @@ __global__ __launch_bounds__(kAttnThreads, 2) void verify_attn16_kernel(AttnPara
         const uint64_t in_range = N == 64 ? ~0ull : ((1ull << N) - 1ull);
         if (lane < N) anc[lane] = P.drafts_visible ? (msk | (peer_bits & in_range)) : 0ull;
     }
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    __syncthreads();
     if (nb > 0) {
-        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-        __syncthreads();
         qk16x4<D>(buf1, ln, qf, s);
         if (S < 64) {
 #pragma unroll
@@ -423,6 +439,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void verify_attn16_kernel(AttnPara
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
         __syncthreads();
     }
+    for (; t < steps_max; ++t) __syncthreads();  // a group with fewer steps meets the others' barriers
 
     // ---------------- phase 2: draft blocks on the root path ----------------
     int nd = 0;
@@ -431,12 +448,44 @@ __global__ __launch_bounds__(kAttnThreads, 2) void verify_attn16_kernel(AttnPara
     const DraftArgs da = draft_args<D>(P, b, g, lane, my_anc, row_valid, q);
     uint16_t* kw = (wave < 2 ? buf0 : buf1) + (wave & 1) * G::kWaveRegionElems;
     TileWalk walk{uniform64(wave_or64(my_anc)), 0, -1};
+    int turn = 0;
     for (int tt = walk.next(L); tt >= 0; tt = walk.next(L)) {
+        if (KG > 1 && turn++ % KG != kg) continue;  // uniform
         wave_lds_sync();
         draft_tile_dma<D, 16>(da, tt * 32, kw, kw + 32 * D);
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
         wave_lds_sync();
         draft_tile16<D>(da, tt * 32, q, kw, kw + 32 * D, ln, qf, st, o, c, thr);
+    }
+
+    // ---------------- merge the key groups ----------------
+    // wave w of every group holds the same rows in the same lanes; a wave's state goes to its own
+    // draft tile region (64 lanes x (D / 4 + 2) floats fit it)
+    if (KG > 1) {
+        constexpr int NF = D / 4;  // output values per lane
+        static_assert(64 * (NF + 2) * 4 <= G::kWaveRegionElems * 2, "a wave's state fits its draft region");
+        wave_lds_sync();
+        if (kg > 0) {
+            float* f = reinterpret_cast<float*>(kw) + lane;
+#pragma unroll
+            for (int i = 0; i < NF; ++i) f[64 * i] = o[i >> 2][i & 3];
+            f[64 * NF] = st.m;
+            f[64 * (NF + 1)] = st.lsum;
+        }
+        __syncthreads();
+        if (kg > 0) return;
+#pragma unroll
+        for (int og = 1; og < KG; ++og) {
+            const float* f = reinterpret_cast<const float*>(kw + og * G::kStageElems) + lane;
+            const float m2 = f[64 * NF], l2 = f[64 * (NF + 1)];
+            const float m = fmaxf(st.m, m2);
+            const float a1 = st.m == kNegInf ? 0.f : fast_exp2((st.m - m) * c);
+            const float a2 = m2 == kNegInf ? 0.f : fast_exp2((m2 - m) * c);
+#pragma unroll
+            for (int i = 0; i < NF; ++i) o[i >> 2][i & 3] = o[i >> 2][i & 3] * a1 + f[64 * i] * a2;
+            st.lsum = st.lsum * a1 + l2 * a2;
+            st.m = m;
+        }
     }
 
     // ---------------- epilogue ----------------

@@ -117,6 +117,23 @@ def test_wrong_mask_is_detected(name):
     assert not ok
 
 
+# 16-row grids split their cache steps (64 keys) over two groups of waves from 193 keys on: either side
+# of that line, even and odd step counts, ragged last steps, and draft tiles shared out one by one
+# (L = 8: four drafts in a tile; L = 33: tiles mixing drafts).
+@pytest.mark.parametrize("S", [192, 193, 255, 256, 257, 320, 321, 705])
+@pytest.mark.parametrize("L,N,Hq,Hkv,D", [(8, 6, 4, 4, 64), (33, 4, 6, 2, 128)])
+@pytest.mark.parametrize("variant", ["spec", "sharp"])
+def test_key_groups(S, L, N, Hq, Hkv, D, variant):
+    wl = Workload(99, "groups", B=2, N=N, L=L, Hq=Hq, Hkv=Hkv, D=D, S_prefix=S, S_suffix=0, V=64,
+                  logits_dtype="f32", margin_max=3.0, parents=None, level_sizes=None)
+    assert _tiling_batch(wl, "16") == 2
+    rng = np.random.default_rng(S + L)
+    parent = np.array([[-1] + [int(rng.integers(-1, n)) for n in range(1, N)] for _ in range(2)], dtype=np.int32)
+    inputs, parent, out = _run(wl, S + N, variant, parent=parent)
+    ok, worst, frac = _check(out, inputs, parent, variant)
+    assert ok, f"S={S}: worst excess {worst:.3g}, {frac:.2%} outside tolerance"
+
+
 @pytest.mark.parametrize("tiling", ["16", "32"])
 @pytest.mark.parametrize("L,N,S,Hq,Hkv,D", [
     (8, 4, 192, 4, 4, 64),      # rows of one wave span 4 drafts
