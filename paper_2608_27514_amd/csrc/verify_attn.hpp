@@ -291,24 +291,29 @@ struct AttnLane {
 // scores are masked or never computed; the clamped values stay finite); the uniform base row
 // is clamped too, so a lane's offset from it is never negative.
 template <int D, bool RAGGED, bool IS_V, int R = 32, typename LaneT>
+__device__ __forceinline__ void cache_row_dma(__amdgpu_buffer_rsrc_t rs, int kv_stride, int key0, int S, int wave,
+                                              const LaneT& ln, uint16_t* dst, int j) {
+    using G = AttnGeom<D, R>;
+    const int row0 = wave * (kAttnTile / kAttnWaves) + j * G::kRowsPerDma;  // uniform
+    const int r = row0 + ln.ri;                                               // tile row
+    int base_row = key0 + row0;
+    int grow = ln.ri;
+    if (RAGGED) {
+        base_row = min(base_row, S - 1);
+        grow = min(key0 + r, S - 1) - base_row;
+    }
+    const int swz = IS_V ? G::v_rot(r) : G::k_swz(r);
+    const unsigned voff = 2u * (unsigned)(grow * kv_stride + ((ln.pc ^ swz) << 3));  // lane bytes
+    const unsigned soff = 2u * (unsigned)(base_row * kv_stride);                     // uniform bytes
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + row0 * D), 16, voff, soff, 0, 0);
+}
+
+template <int D, bool RAGGED, bool IS_V, int R = 32, typename LaneT>
 __device__ __forceinline__ void cache_rows_dma(__amdgpu_buffer_rsrc_t rs, int kv_stride, int key0, int S, int wave,
                                                const LaneT& ln, uint16_t* dst) {
-    using G = AttnGeom<D, R>;
 #pragma unroll
-    for (int j = 0; j < G::kDmaPerWave; ++j) {
-        const int row0 = wave * (kAttnTile / kAttnWaves) + j * G::kRowsPerDma;  // uniform
-        const int r = row0 + ln.ri;                                               // tile row
-        int base_row = key0 + row0;
-        int grow = ln.ri;
-        if (RAGGED) {
-            base_row = min(base_row, S - 1);
-            grow = min(key0 + r, S - 1) - base_row;
-        }
-        const int swz = IS_V ? G::v_rot(r) : G::k_swz(r);
-        const unsigned voff = 2u * (unsigned)(grow * kv_stride + ((ln.pc ^ swz) << 3));  // lane bytes
-        const unsigned soff = 2u * (unsigned)(base_row * kv_stride);                     // uniform bytes
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + row0 * D), 16, voff, soff, 0, 0);
-    }
+    for (int j = 0; j < AttnGeom<D, R>::kDmaPerWave; ++j)
+        cache_row_dma<D, RAGGED, IS_V, R>(rs, kv_stride, key0, S, wave, ln, dst, j);
 }
 
 // Stage t of the cache pipeline holds the V rows of keys 64 t .. 64 t + 63 (blocks 2t, 2t+1) and
@@ -321,6 +326,17 @@ __device__ __forceinline__ void stage_dma(__amdgpu_buffer_rsrc_t krs, __amdgpu_b
     using G = AttnGeom<D, R>;
     cache_rows_dma<D, RAGGED, false, R>(krs, kv_stride, t * kAttnTile + kAttnTile, S, wave, ln, stage);
     cache_rows_dma<D, RAGGED, true, R>(vrs, kv_stride, t * kAttnTile, S, wave, ln, stage + G::kTileElems);
+}
+
+// Load i of a full stage t (the K rows' loads, then the V rows').
+template <int D, int R = 32, typename LaneT>
+__device__ __forceinline__ void stage_dma_one(__amdgpu_buffer_rsrc_t krs, __amdgpu_buffer_rsrc_t vrs, int kv_stride, int t,
+                                              int S, int wave, const LaneT& ln, uint16_t* stage, int i) {
+    using G = AttnGeom<D, R>;
+    if (i < G::kDmaPerWave)
+        cache_row_dma<D, false, false, R>(krs, kv_stride, t * kAttnTile + kAttnTile, S, wave, ln, stage, i);
+    else
+        cache_row_dma<D, false, true, R>(vrs, kv_stride, t * kAttnTile, S, wave, ln, stage + G::kTileElems, i - G::kDmaPerWave);
 }
 
 // Softmax phase of a 64-key step: the weights of two blocks (s[0], s[1]) against the query's
@@ -436,10 +452,10 @@ __device__ __forceinline__ void pv_pair(const uint16_t* vbase, const AttnLane<D>
 // and O += V P of the current pair from the V rows at vbase.  As in qk_pair / pv_pair every
 // fragment read follows an MFMA; the V fragments of the first group ride on the last QK MFMAs,
 // which have no K reads left to carry.
-template <int D>
+template <int D, typename Side>
 __device__ __forceinline__ void matrix_pair(const uint16_t* kbase, const uint16_t* vbase, const AttnLane<D>& ln,
                                             const bf16x8_t (&qf)[D / 16], f32x16_t (&sn)[2], const bf16x8_t (&pf)[2][2],
-                                            f32x16_t (&o)[D / 32]) {
+                                            f32x16_t (&o)[D / 32], Side side) {
     constexpr int KS = D / 16;
     constexpr int NDB = D / 32;
     static_assert(2 * 2 >= NDB, "the last two QK steps carry the first V group");
@@ -466,6 +482,7 @@ __device__ __forceinline__ void matrix_pair(const uint16_t* kbase, const uint16_
             const int db = 2 * (ks + 2 - KS);
             if (db < NDB) read_v(0, db, va[0][db]);
         }
+        side(2 * ks);
         __builtin_amdgcn_sched_barrier(0);
         b = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb[ks], qf[ks], b, 0, 0, 0);
         if (ks + 2 < KS) {
@@ -474,6 +491,7 @@ __device__ __forceinline__ void matrix_pair(const uint16_t* kbase, const uint16_
             const int db = 2 * (ks + 2 - KS) + 1;
             if (db < NDB) read_v(0, db, va[0][db]);
         }
+        side(2 * ks + 1);
         __builtin_amdgcn_sched_barrier(0);
     }
     sn[0] = a;
@@ -484,6 +502,7 @@ __device__ __forceinline__ void matrix_pair(const uint16_t* kbase, const uint16_
         for (int db = 0; db < NDB; ++db) {
             o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[grp & 1][db], pf[grp >> 1][grp & 1], o[db], 0, 0, 0);
             if (grp + 1 < 4) read_v(grp + 1, db, va[(grp + 1) & 1][db]);
+            side(2 * KS + grp * NDB + db);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -507,18 +526,21 @@ __device__ __forceinline__ void full_step(int t, const CacheArgs& a, const AttnL
                                           uint16_t* nxt, const bf16x8_t (&qf)[D / 16], f32x16_t (&s)[2], SoftState& st,
                                           f32x16_t (&o)[D / 32]) {
     using G = AttnGeom<D>;
-    stage_dma<D, false>(a.krs, a.vrs, a.kv_stride, t + 1, a.S, a.wave, ln, nxt);
+    constexpr int NM = 2 * (D / 16) + 4 * (D / 32), NL = 2 * G::kDmaPerWave;
     bf16x8_t pf[2][2];
     softmax_phase<D>(s, a.c, a.thr, st, o, pf);
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    __syncthreads();
     __builtin_amdgcn_sched_barrier(0);
     // the matrix phase issues at a raised wave priority: when the other wave on the SIMD is in
     // its softmax phase, the arbiter then keeps the matrix core fed first (-6% on 8b-batched)
     __builtin_amdgcn_s_setprio(1);
-    matrix_pair<D>(cur, cur + G::kTileElems, ln, qf, s, pf, o);
+    matrix_pair<D>(cur, cur + G::kTileElems, ln, qf, s, pf, o, [&](int i) {
+        if ((i + 1) * NL / NM > i * NL / NM)
+            stage_dma_one<D>(a.krs, a.vrs, a.kv_stride, t + 1, a.S, a.wave, ln, nxt, i * NL / NM);
+    });
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_setprio(0);
-    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-    __syncthreads();
 }
 
 // Ascending walk over the 32-key draft tiles that hold a block of `todo` (a wave-uniform set of
@@ -783,7 +805,6 @@ __global__ __launch_bounds__(kAttnThreads, 2) void verify_attn_kernel(AttnParams
             mask_tail(s[1], 32, S, h);
         }
     }
-    __syncthreads();  // buf1 free for stage 1; the ancestor masks visible
     int t = 0;
     // Step pairs whose next stages are full: buffers known at compile time, no conditional code.
     for (; 64 * t + 256 <= S; t += 2) {
@@ -796,6 +817,11 @@ __global__ __launch_bounds__(kAttnThreads, 2) void verify_attn_kernel(AttnParams
     for (; t < nst; ++t) {
         uint16_t* cur = (t & 1) ? buf1 : buf0;
         uint16_t* nxt = (t & 1) ? buf0 : buf1;
+        bf16x8_t pf[2][2];
+        softmax_phase<D>(s, c, thr, st, o, pf);
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
         if (t + 1 < nst) {
             if (64 * t + 192 <= S) {
                 stage_dma<D, false>(ca.krs, ca.vrs, kv_stride, t + 1, S, wave, ln, nxt);
@@ -803,9 +829,6 @@ __global__ __launch_bounds__(kAttnThreads, 2) void verify_attn_kernel(AttnParams
                 stage_dma<D, true>(ca.krs, ca.vrs, kv_stride, t + 1, S, wave, ln, nxt);
             }
         }
-        bf16x8_t pf[2][2];
-        softmax_phase<D>(s, c, thr, st, o, pf);
-        __builtin_amdgcn_sched_barrier(0);
         if (2 * t + 2 < nb) {
             qk_pair<D>(cur, ln, qf, s);
             if (64 * t + 128 > S) {
@@ -814,9 +837,8 @@ __global__ __launch_bounds__(kAttnThreads, 2) void verify_attn_kernel(AttnParams
             }
         }
         pv_pair<D>(cur + G::kTileElems, ln, pf, o);
-        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-        __syncthreads();
     }
+    __syncthreads();  // the stage buffers are free for the waves' draft tiles; the ancestor masks visible
 
     // ---------------- phase 2: draft blocks on the root path ----------------
     int nd = 0;

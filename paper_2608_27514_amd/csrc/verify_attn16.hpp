@@ -167,10 +167,10 @@ __device__ __forceinline__ void pv16x2(const uint16_t* vbase, const AttnLane16<D
 
 // Matrix phase of a full step: scores of the next four blocks (K rows at kbase) and O += V P of
 // the current 64 keys (V rows at vbase); the first two V fragments ride on the last score MFMAs.
-template <int D>
+template <int D, typename Side>
 __device__ __forceinline__ void matrix16(const uint16_t* kbase, const uint16_t* vbase, const AttnLane16<D>& ln,
                                          const bf16x8_t (&qf)[D / 32], f32x4_t (&sn)[4], const bf16x8_t (&pf)[2],
-                                         f32x4_t (&o)[D / 16]) {
+                                         f32x4_t (&o)[D / 16], Side side) {
     constexpr int KS = D / 32;
     constexpr int NK = 4 * KS;
     constexpr int NDB = D / 16;
@@ -189,6 +189,7 @@ __device__ __forceinline__ void matrix16(const uint16_t* kbase, const uint16_t* 
             const int m = n + 2 - NK;  // 0, 1
             va[m] = v_frag16<D>(vbase, ln, m);
         }
+        side(n);
         __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
@@ -197,6 +198,7 @@ __device__ __forceinline__ void matrix16(const uint16_t* kbase, const uint16_t* 
     for (int m = 0; m < NV; ++m) {
         o[m % NDB] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[m], pf[m / NDB], o[m % NDB], 0, 0, 0);
         if (m + 2 < NV) va[m + 2] = v_frag16<D>(vbase + ((m + 2) / NDB) * 32 * D, ln, (m + 2) % NDB);
+        side(NK + m);
         __builtin_amdgcn_sched_barrier(0);
     }
 }
@@ -207,16 +209,19 @@ __device__ __forceinline__ void full_step16(int t, const CacheArgs& a, const Att
                                             uint16_t* nxt, const bf16x8_t (&qf)[D / 32], f32x4_t (&s)[4],
                                             SoftState& st, f32x4_t (&o)[D / 16]) {
     using G = AttnGeom<D, 16>;
-    stage_dma<D, false, 16>(a.krs, a.vrs, a.kv_stride, t + 1, a.S, a.wave, ln, nxt);
+    constexpr int NM = 4 * (D / 32) + 2 * (D / 16), NL = 2 * G::kDmaPerWave;
     bf16x8_t pf[2];
     softmax16<D>(s, a.c, a.thr, st, o, pf);
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_setprio(1);
-    matrix16<D>(cur, cur + G::kTileElems, ln, qf, s, pf, o);
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     __syncthreads();
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+    matrix16<D>(cur, cur + G::kTileElems, ln, qf, s, pf, o, [&](int i) {
+        if ((i + 1) * NL / NM > i * NL / NM)
+            stage_dma_one<D, 16>(a.krs, a.vrs, a.kv_stride, t + 1, a.S, a.wave, ln, nxt, i * NL / NM);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(0);
 }
 
 // Scores, weights and O += V P of the draft tile k0 .. k0+31 held in the wave's regions kw, vw.
@@ -409,7 +414,6 @@ __global__ __launch_bounds__(kAttnThreads* KG, 2 / KG) void verify_attn16_kernel
             for (int j = 0; j < 4; ++j) mask_tail16(s[j], 16 * j, S, q);
         }
     }
-    __syncthreads();
     int t = 0;
     for (; 64 * t + 256 <= S; t += 2) {
         full_step16<D>(t, ca, ln, buf0, buf1, qf, s, st, o);
@@ -418,6 +422,11 @@ __global__ __launch_bounds__(kAttnThreads* KG, 2 / KG) void verify_attn16_kernel
     for (; t < nst; ++t) {
         uint16_t* cur = (t & 1) ? buf1 : buf0;
         uint16_t* nxt = (t & 1) ? buf0 : buf1;
+        bf16x8_t pf[2];
+        softmax16<D>(s, c, thr, st, o, pf);
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
         if (t + 1 < nst) {
             if (64 * t + 192 <= S) {
                 stage_dma<D, false, 16>(ca.krs, ca.vrs, kv_stride, t + 1, S, wave, ln, nxt);
@@ -425,9 +434,6 @@ __global__ __launch_bounds__(kAttnThreads* KG, 2 / KG) void verify_attn16_kernel
                 stage_dma<D, true, 16>(ca.krs, ca.vrs, kv_stride, t + 1, S, wave, ln, nxt);
             }
         }
-        bf16x8_t pf[2];
-        softmax16<D>(s, c, thr, st, o, pf);
-        __builtin_amdgcn_sched_barrier(0);
         if (2 * t + 2 < nb) {
             qk16x4<D>(cur, ln, qf, s);
             if (64 * t + 128 > S) {
@@ -436,10 +442,9 @@ __global__ __launch_bounds__(kAttnThreads* KG, 2 / KG) void verify_attn16_kernel
             }
         }
         pv16x2<D>(cur + G::kTileElems, ln, pf, o);
-        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-        __syncthreads();
     }
     for (; t < steps_max; ++t) __syncthreads();  // a group with fewer steps meets the others' barriers
+    __syncthreads();  // the stage buffers are free for the waves' draft tiles; the ancestor masks visible
 
     // ---------------- phase 2: draft blocks on the root path ----------------
     int nd = 0;
