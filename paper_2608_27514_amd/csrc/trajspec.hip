@@ -80,6 +80,10 @@ int device_cu_count() {
 // half the chain of steps each): 736 keys 16.9 -> 14.9 us, 4096 keys 54.5 -> 45.3 (8 drafts x 32
 // heads), 256 keys 10.6 -> 10.2; at 192 keys and below the merge costs what the steps save.
 constexpr int kAttnSplitKeysMin = 192;
+// The same for 32-row grids of at most one workgroup per CU, from this many keys on: 16 drafts of 64
+// over 2048 keys (28 x 4 heads) 39.8 -> 38.2 us, 32 x 32 over 1504 (32 heads) 36.3 -> 34.4, a
+// sequence of 768 over itself 43.7 -> 37.5; 512 keys 19.7 -> 19.6, 256 keys 15.6 -> 16.3.
+constexpr int kAttnSplitKeysMin32 = 512;
 
 // p describes the 32-row launch (4 waves x 32 rows per workgroup).  A grid that still has at
 // most one workgroup per CU with 16-row waves (4 waves x 16 rows per workgroup, twice the
@@ -98,7 +102,10 @@ traj_status launch_attn(AttnParams p, hipStream_t st) {
         else
             hipLaunchKernelGGL((verify_attn16_kernel<D, 1>), dim3(p.num_wg), dim3(kAttnThreads), 0, st, p);
     } else {
-        hipLaunchKernelGGL(verify_attn_kernel<D>, dim3(p.num_wg), dim3(kAttnThreads), 0, st, p);
+        if (p.num_wg <= device_cu_count() && p.S >= kAttnSplitKeysMin32)
+            hipLaunchKernelGGL((verify_attn_kernel<D, 2>), dim3(p.num_wg), dim3(2 * kAttnThreads), 0, st, p);
+        else
+            hipLaunchKernelGGL((verify_attn_kernel<D, 1>), dim3(p.num_wg), dim3(kAttnThreads), 0, st, p);
     }
     return launched();
 }

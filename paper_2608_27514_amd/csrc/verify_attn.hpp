@@ -37,13 +37,17 @@
 //      other's matrix phase.  Stage t holds the V rows of blocks 2t, 2t+1 and the K rows of
 //      blocks 2t+2, 2t+3 in one of two LDS buffers (separate arrays, so the compiler can see
 //      that the direct loads into one never alias reads of the other); the next stage loads
-//      during the current step, one barrier per step.  Step pairs whose next stages are full
+//      during the current step, one barrier per step (between its softmax and matrix phases, whose
+//      MFMAs the next stage's loads are issued between).  Step pairs whose next stages are full
 //      run with no conditional code; the last steps mask the scores of keys past S.
 //   2. drafts: each wave visits only the 32-key tiles holding its own block or an ancestor
 //      block (the set bits of the OR of its rows' ancestor masks, lowest first); optional
 //      per-draft peer masks add drafts to a draft's visible set (inter-block speculation).
 //      Tiles that hold only fully visible blocks need no per-element mask (always the case
 //      when L is a multiple of 32 and a wave's rows share a draft).
+//   3. with KG key groups of 4 waves (grids of at most one workgroup per CU over longer caches):
+//      group kg takes its own range of cache steps and every KG-th draft tile, and the groups'
+//      outputs, references and sums are merged through LDS.
 //   With drafts_visible = 0 every visible set is empty and phase 2 does nothing: the queries
 //   attend to the S cache keys only.  The dual-cache refresh uses this for bidirectional
 //   attention over whole sequences (its "cache" is the sequence's own K / V, N = 1 and L = the
@@ -515,12 +519,13 @@ struct CacheArgs {
     float c, thr;
 };
 
-// One 64-key step t of the cache phase whose next stage is full (64 t + 192 <= S): the loads of
-// stage t+1 go out, the softmax phase turns the scores of blocks 2t, 2t+1 into weights, the
-// matrix phase computes the scores of blocks 2t+2, 2t+3 and adds the weighted V rows of blocks
-// 2t, 2t+1.  Ends with the loads retired and a barrier.  Two waves of different workgroups
-// share each SIMD: one's softmax phase runs on the vector ALU while the other's matrix phase
-// runs on the matrix core.
+// One 64-key step t of the cache phase whose next stage is full (64 t + 192 <= S): the softmax
+// phase turns the scores of blocks 2t, 2t+1 into weights; once every wave's loads of stage t have
+// landed (wait and barrier), the matrix phase computes the scores of blocks 2t+2, 2t+3, adds the
+// weighted V rows of blocks 2t, 2t+1 and issues the loads of stage t+1 between its MFMAs (issued
+// together before the softmax they held it up: the load path takes one per ~16 cycles and CU).
+// Two waves share each SIMD: one's softmax phase runs on the vector ALU while the other's matrix
+// phase runs on the matrix core.
 template <int D>
 __device__ __forceinline__ void full_step(int t, const CacheArgs& a, const AttnLane<D>& ln, const uint16_t* cur,
                                           uint16_t* nxt, const bf16x8_t (&qf)[D / 16], f32x16_t (&s)[2], SoftState& st,
@@ -658,16 +663,20 @@ __device__ __forceinline__ void draft_tile(const DraftArgs& a, int k0, const uin
     pv_block<D>(vw, ln.vq, pf, o);
 }
 
-template <int D>
-__global__ __launch_bounds__(kAttnThreads, 2) void verify_attn_kernel(AttnParams P) {
+template <int D, int KG>
+__global__ __launch_bounds__(kAttnThreads* KG, 2 / KG) void verify_attn_kernel(AttnParams P) {
     using G = AttnGeom<D>;
-    __shared__ __attribute__((aligned(1024))) uint16_t buf0[G::kStageElems];
-    __shared__ __attribute__((aligned(1024))) uint16_t buf1[G::kStageElems];
+    __shared__ __attribute__((aligned(1024))) uint16_t buf0_all[KG * G::kStageElems];
+    __shared__ __attribute__((aligned(1024))) uint16_t buf1_all[KG * G::kStageElems];
     __shared__ uint64_t anc[64];
+    __shared__ float merge_m[KG > 1 ? (KG - 1) * kAttnThreads : 1], merge_l[KG > 1 ? (KG - 1) * kAttnThreads : 1];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform per wave
+    const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform per wave
+    const int wave = wave_all % kAttnWaves, kg = wave_all / kAttnWaves;  // wave within its key group
+    uint16_t* buf0 = buf0_all + kg * G::kStageElems;
+    uint16_t* buf1 = buf1_all + kg * G::kStageElems;
     const int h = lane >> 5;
 
     const int lid = xcd_logical_id(blockIdx.x, P.num_wg);
@@ -675,14 +684,14 @@ __global__ __launch_bounds__(kAttnThreads, 2) void verify_attn_kernel(AttnParams
     const int bg = lid / P.wg_per_group;
     const int g = bg % P.Hkv;
     const int b = bg / P.Hkv;
-    const int N = P.N, L = P.L, S = P.S;
+    const int N = P.N, L = P.L;
     const float c = P.scale_log2;
     const float thr = kLazyLog2 / c;  // lazy-rescale margin in raw score units
 
     // The parent array (ancestor walk below) is loaded first: the walk then waits for this
     // load only, not for the Q, K and stage loads issued after it.
-    const int pj = (P.parent != nullptr && wave == 0 && lane < N) ? P.parent[(int64_t)b * N + lane] : -1;
-    const uint64_t peer_bits = (P.peers != nullptr && wave == 0 && lane < N) ? P.peers[(int64_t)b * N + lane] : 0ull;
+    const int pj = (P.parent != nullptr && wave_all == 0 && lane < N) ? P.parent[(int64_t)b * N + lane] : -1;
+    const uint64_t peer_bits = (P.peers != nullptr && wave_all == 0 && lane < N) ? P.peers[(int64_t)b * N + lane] : 0ull;
 
     // This lane's query row (lanes l and l^32 share a row).
     const int row = (wg_in_group * kAttnWaves + wave) * 32 + (lane & 31);
@@ -734,16 +743,21 @@ __global__ __launch_bounds__(kAttnThreads, 2) void verify_attn_kernel(AttnParams
     SoftState st = {kNegInf, 0.f, kNegInf, 0.f};
 
     // ---------------- phase 1: cache keys ----------------
+    // this group's keys: steps [kg steps_max, (kg + 1) steps_max) of the cache
+    const int steps_max = ((P.S + kAttnTile - 1) / kAttnTile + KG - 1) / KG;
+    const int key_first = min(kg * steps_max * kAttnTile, P.S);
+    const int S = min(steps_max * kAttnTile, P.S - key_first);
     CacheArgs ca;
     {
         // descriptors over this (b, g) slice to the end of the tensor (the host guarantees one
         // sequence's cache spans less than 2^31 bytes, so row offsets fit the 32-bit soffset)
-        const uint16_t* kc_base = P.kc + ((int64_t)b * S * P.Hkv + g) * D;
-        const uint16_t* vc_base = P.vc + ((int64_t)b * S * P.Hkv + g) * D;
-        const int64_t total = (int64_t)P.B * S * P.Hkv * D * 2;
-        const int64_t start = ((int64_t)b * S * P.Hkv + g) * D * 2;
+        const int64_t first = (((int64_t)b * P.S + key_first) * P.Hkv + g) * D;
+        const uint16_t* kc_base = P.kc + first;
+        const uint16_t* vc_base = P.vc + first;
+        const int64_t total = (int64_t)P.B * P.S * P.Hkv * D * 2;
+        const int64_t start = first * 2;
         const int64_t rem = total - start;
-        const int nrec = rem > 0x7FFFFFFF ? 0x7FFFFFFF : (int)rem;
+        const int nrec = rem > 0x7FFFFFFF ? 0x7FFFFFFF : rem < 0 ? 0 : (int)rem;
         ca.krs = __builtin_amdgcn_make_buffer_rsrc((void*)kc_base, (short)0, nrec, kBufferFlags);
         ca.vrs = __builtin_amdgcn_make_buffer_rsrc((void*)vc_base, (short)0, nrec, kBufferFlags);
     }
@@ -773,7 +787,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void verify_attn_kernel(AttnParams
     // Ancestor masks (bit j of anc[n] set when draft j is n itself or on n's root path).  Wave 0
     // holds the sequence's parent array (N <= 64 = one value per lane) and every lane walks
     // its own draft's chain through lane shuffles, so the walk costs no dependent global loads.
-    if (wave == 0) {
+    if (wave_all == 0) {
         uint64_t msk = 1ull << lane;
         int j = pj, prev = lane;
         bool live = lane < N;
@@ -796,9 +810,9 @@ __global__ __launch_bounds__(kAttnThreads, 2) void verify_attn_kernel(AttnParams
         const uint64_t in_range = N == 64 ? ~0ull : ((1ull << N) - 1ull);
         if (lane < N) anc[lane] = P.drafts_visible ? (msk | (peer_bits & in_range)) : 0ull;
     }
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    __syncthreads();
     if (nb > 0) {
-        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-        __syncthreads();
         qk_pair<D>(buf1, ln, qf, s);
         if (S < 64) {
             mask_tail(s[0], 0, S, h);
@@ -838,6 +852,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void verify_attn_kernel(AttnParams
         }
         pv_pair<D>(cur + G::kTileElems, ln, pf, o);
     }
+    for (; t < steps_max; ++t) __syncthreads();  // a group with fewer steps meets the others' barriers
     __syncthreads();  // the stage buffers are free for the waves' draft tiles; the ancestor masks visible
 
     // ---------------- phase 2: draft blocks on the root path ----------------
@@ -849,12 +864,44 @@ __global__ __launch_bounds__(kAttnThreads, 2) void verify_attn_kernel(AttnParams
     // tile is loaded into the wave's region, then multiplied.
     uint16_t* kw = (wave < 2 ? buf0 : buf1) + (wave & 1) * G::kWaveRegionElems;
     TileWalk walk{uniform64(wave_or64(my_anc)), 0, -1};
+    int turn = 0;
     for (int tt = walk.next(L); tt >= 0; tt = walk.next(L)) {
+        if (KG > 1 && turn++ % KG != kg) continue;  // uniform: the groups take the tiles in turn
         wave_lds_sync();
         draft_tile_dma<D>(da, tt * 32, kw, kw + 32 * D);
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
         wave_lds_sync();
         draft_tile<D>(da, tt * 32, kw, kw + 32 * D, ln, qf, st, o, c, thr);
+    }
+
+    // ---------------- merge the key groups ----------------
+    // wave w of every group holds the same rows in the same lanes; a wave's output goes to its own
+    // draft tile region (64 lanes x D / 2 floats fill it)
+    if (KG > 1) {
+        constexpr int NF = D / 2;  // output values per lane
+        static_assert(64 * NF * 4 <= G::kWaveRegionElems * 2, "a wave's output fits its draft region");
+        wave_lds_sync();
+        if (kg > 0) {
+            float* f = reinterpret_cast<float*>(kw) + lane;
+#pragma unroll
+            for (int i = 0; i < NF; ++i) f[64 * i] = o[i >> 4][i & 15];
+            merge_m[tid - kAttnThreads] = st.m;
+            merge_l[tid - kAttnThreads] = st.lsum;
+        }
+        __syncthreads();
+        if (kg > 0) return;
+#pragma unroll
+        for (int og = 1; og < KG; ++og) {
+            const float* f = reinterpret_cast<const float*>(kw + og * G::kStageElems) + lane;
+            const float m2 = merge_m[tid + (og - 1) * kAttnThreads], l2 = merge_l[tid + (og - 1) * kAttnThreads];
+            const float m = fmaxf(st.m, m2);
+            const float a1 = st.m == kNegInf ? 0.f : fast_exp2((st.m - m) * c);
+            const float a2 = m2 == kNegInf ? 0.f : fast_exp2((m2 - m) * c);
+#pragma unroll
+            for (int i = 0; i < NF; ++i) o[i >> 4][i & 15] = o[i >> 4][i & 15] * a1 + f[64 * i] * a2;
+            st.lsum = st.lsum * a1 + l2 * a2;
+            st.m = m;
+        }
     }
 
     // ---------------- epilogue ----------------

@@ -134,6 +134,21 @@ def test_key_groups(S, L, N, Hq, Hkv, D, variant):
     assert ok, f"S={S}: worst excess {worst:.3g}, {frac:.2%} outside tolerance"
 
 
+# The same for 32-row grids of at most one workgroup per CU, from 512 keys on.
+@pytest.mark.parametrize("S", [511, 512, 513, 575, 640, 641, 833])
+@pytest.mark.parametrize("L,N,Hq,Hkv,D", [(8, 16, 4, 4, 64), (33, 4, 6, 2, 128)])
+def test_key_groups_of_32_rows(S, L, N, Hq, Hkv, D):
+    wl = Workload(99, "groups", B=2, N=N, L=L, Hq=Hq, Hkv=Hkv, D=D, S_prefix=S, S_suffix=0, V=64,
+                  logits_dtype="f32", margin_max=3.0, parents=None, level_sizes=None)
+    B = _tiling_batch(wl, "32")
+    assert B * Hkv * -(-((Hq // Hkv) * N * L) // 128) <= _cus()
+    rng = np.random.default_rng(S + L)
+    parent = np.array([[-1] + [int(rng.integers(-1, n)) for n in range(1, N)] for _ in range(B)], dtype=np.int32)
+    inputs, parent, out = _run(wl.with_(B=B), S + N, "sharp", parent=parent)
+    ok, worst, frac, b = _check_seqs(out, inputs, parent, "sharp", (0, B - 1))
+    assert ok, f"S={S} sequence {b}: worst excess {worst:.3g}, {frac:.2%} outside tolerance"
+
+
 @pytest.mark.parametrize("tiling", ["16", "32"])
 @pytest.mark.parametrize("L,N,S,Hq,Hkv,D", [
     (8, 4, 192, 4, 4, 64),      # rows of one wave span 4 drafts
