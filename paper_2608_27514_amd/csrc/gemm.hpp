@@ -456,15 +456,27 @@ __global__ __launch_bounds__(WM* WN * 64, 1) void gemm_ring_kernel(GemmParams P)
     gemm_epilogue<BM, BN, WM, WN, EPI>(P, acc, lds, m0, n0);
 }
 
-// Sum over the splits of 8 partial products from element e0.
+constexpr int kGemmMaxSplits = 8;
+
+// Sum over the splits of 8 partial products from element e0, in split order.  Every split's loads are
+// requested before the first is added.
 __device__ __forceinline__ void split_sum8(const float* __restrict__ partial, int splits, int64_t MN, int64_t e0, float (&v)[8]) {
+    float4 lo[kGemmMaxSplits], hi[kGemmMaxSplits];
+#pragma unroll
+    for (int s = 0; s < kGemmMaxSplits; ++s) {
+        if (s < splits) {  // uniform
+            lo[s] = *reinterpret_cast<const float4*>(partial + s * MN + e0);
+            hi[s] = *reinterpret_cast<const float4*>(partial + s * MN + e0 + 4);
+        }
+    }
 #pragma unroll
     for (int i = 0; i < 8; ++i) v[i] = 0.f;
-    for (int s2 = 0; s2 < splits; ++s2) {
-        const float4 lo = *reinterpret_cast<const float4*>(partial + s2 * MN + e0);
-        const float4 hi = *reinterpret_cast<const float4*>(partial + s2 * MN + e0 + 4);
-        v[0] += lo.x; v[1] += lo.y; v[2] += lo.z; v[3] += lo.w;
-        v[4] += hi.x; v[5] += hi.y; v[6] += hi.z; v[7] += hi.w;
+#pragma unroll
+    for (int s = 0; s < kGemmMaxSplits; ++s) {
+        if (s < splits) {
+            v[0] += lo[s].x; v[1] += lo[s].y; v[2] += lo[s].z; v[3] += lo[s].w;
+            v[4] += hi[s].x; v[5] += hi[s].y; v[6] += hi[s].z; v[7] += hi[s].w;
+        }
     }
 }
 

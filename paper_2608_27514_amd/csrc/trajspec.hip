@@ -206,7 +206,6 @@ const GemmTiling kGemmTilings[] = {
 #undef TRAJ_RING_TILING
 
 constexpr int kGemmCus = 256;           // workgroups the chip runs at a time
-constexpr int kGemmMaxSplits = 8;
 constexpr int64_t kGemmMinSplitK = 512;
 // SwiGLU goes into the GEMM's own epilogue from this many rows on: there the projection is bound
 // by the matrix cores and the gate / up values' round trip through memory costs as much as it
@@ -271,8 +270,10 @@ size_t gemm_swiglu_workspace_bytes(int64_t M, int64_t N, int64_t K) {
 // D[M,N] = A[M,K] W[K,N] (+ D with kEpiAccumulate), or with kEpiSwiglu D[M,N/2] = silu(gate) * up
 // of the product's [gate | up] columns; bf16 row-major, fp32 accumulation.  `ws` holds the split-K
 // partials (may be null or too small except for SwiGLU: the shape then runs unsplit).
+// With `pending` a split leaves its sum to the caller: *pending is the number of partial products in
+// ws (1: D holds the result).
 traj_status gemm(const uint16_t* A, const uint16_t* W, uint16_t* D, int64_t M, int64_t N, int64_t K, GemmEpilogue epi,
-                 void* ws, size_t ws_bytes, hipStream_t st) {
+                 void* ws, size_t ws_bytes, hipStream_t st, int* pending = nullptr) {
     if (M < 1 || N < 8 || K < 8 || N % 8 != 0 || K % 8 != 0) return TRAJ_E_SHAPE;
     if (M > INT_MAX - kG2BM) return TRAJ_E_SHAPE;
     if (K > kGemmMaxK || N > kGemmMaxN) return TRAJ_E_UNSUPPORTED;  // 32-bit buffer offsets
@@ -290,7 +291,8 @@ traj_status gemm(const uint16_t* A, const uint16_t* W, uint16_t* D, int64_t M, i
     hipLaunchKernelGGL(g.tiling->kernel[g.splits > 1 ? kEpiPartial : apart ? kEpiStore : epi], grid, dim3(g.tiling->threads), 0,
                        st, p);
     const traj_status rs = launched();
-    if (rs != TRAJ_OK || (g.splits == 1 && !apart)) return rs;
+    if (pending != nullptr) *pending = g.splits;
+    if (rs != TRAJ_OK || (g.splits == 1 && !apart) || (g.splits > 1 && pending != nullptr)) return rs;
     const int64_t chunks = M * (swiglu ? N / 2 : N) / 8;
     const dim3 rgrid((unsigned)std::min<int64_t>((chunks + 255) / 256, 4096));
     if (apart) {
@@ -398,6 +400,26 @@ traj_status attn_cache_only(const uint16_t* q, const uint16_t* k, const uint16_t
     return D == 128 ? launch_attn<128>(p, s) : launch_attn<64>(p, s);
 }
 
+// out = norm(x) * w over T rows; with splits > 1 x first gains the sum of the partial products.
+template <bool SPLIT>
+traj_status launch_rmsnorm(uint16_t* x, const void* w, uint16_t* out, int64_t T, int hidden, float eps, const float* partial,
+                           int splits, hipStream_t s) {
+    const int nv = hidden / 8;
+    auto kernel = nv <= 256    ? rmsnorm_kernel<256, 1, SPLIT>
+                  : nv <= 512  ? rmsnorm_kernel<512, 1, SPLIT>
+                  : nv <= 1024 ? rmsnorm_kernel<512, 2, SPLIT>
+                               : rmsnorm_kernel<512, 0, SPLIT>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)T), dim3(nv <= 256 ? 256 : 512), 0, s, x, static_cast<const uint16_t*>(w), out,
+                       hidden, eps, partial, splits);
+    return launched();
+}
+
+traj_status rmsnorm(uint16_t* x, const void* w, uint16_t* out, int64_t T, int hidden, float eps, const float* partial, int splits,
+                    hipStream_t s) {
+    return splits > 1 ? launch_rmsnorm<true>(x, w, out, T, hidden, eps, partial, splits, s)
+                      : launch_rmsnorm<false>(x, w, out, T, hidden, eps, nullptr, 1, s);
+}
+
 // One pre-norm decoder layer over T packed tokens (x [T, hidden], updated in place).  The rotary
 // position of token t is pos0[t / rope_nl] + t % rope_l (pos0 may be null = 0); `attend` runs
 // between the rotary split and the O projection: it reads the q / k / v rows and writes the
@@ -412,25 +434,25 @@ traj_status run_layer(uint16_t* xs, const traj_layer_weights* w, const traj_laye
     void* split = ws + plan.split;
     const size_t split_bytes = plan.split_bytes;
     traj_status st;
+    const float* partial = static_cast<const float*>(split);
     // attention block
-    hipLaunchKernelGGL(rmsnorm_kernel, dim3((unsigned)T), dim3(kLayerThreads), 0, s, xs,
-                       static_cast<const uint16_t*>(w->attn_norm), buf(plan.xn), hidden, dims->rms_eps);
-    if ((st = launched()) != TRAJ_OK) return st;
+    if ((st = rmsnorm(xs, w->attn_norm, buf(plan.xn), T, hidden, dims->rms_eps, nullptr, 1, s)) != TRAJ_OK) return st;
+    int pending = 1;  // partial products the next kernel sums
     if ((st = gemm(buf(plan.xn), static_cast<const uint16_t*>(w->w_qkv), buf(plan.qkv), T, qkv_w, hidden, kEpiStore, split,
-                   split_bytes, s)) != TRAJ_OK)
+                   split_bytes, s, &pending)) != TRAJ_OK)
         return st;
-    hipLaunchKernelGGL(rope_split_kernel, dim3((unsigned)T), dim3(kLayerThreads), 0, s, buf(plan.qkv), pos0,
-                       buf(plan.q), buf(plan.kd), buf(plan.vd), rope_nl, rope_l, Hq, Hkv, D,
-                       std::log2(dims->rope_theta));
+    // few tokens: a chunk pair per thread, so that no thread waits on memory twice
+    const unsigned rope_y = T < 1024 ? (unsigned)((qkv_w / 16 + kLayerThreads - 1) / kLayerThreads) : 1u;
+    hipLaunchKernelGGL(pending > 1 ? rope_split_kernel<true> : rope_split_kernel<false>, dim3((unsigned)T, rope_y),
+                       dim3(kLayerThreads), 0, s, buf(plan.qkv), partial, pending, pos0, buf(plan.q), buf(plan.kd),
+                       buf(plan.vd), rope_nl, rope_l, Hq, Hkv, D, std::log2(dims->rope_theta));
     if ((st = launched()) != TRAJ_OK) return st;
     if ((st = attend(buf(plan.q), buf(plan.kd), buf(plan.vd), buf(plan.a))) != TRAJ_OK) return st;
     if ((st = gemm(buf(plan.a), static_cast<const uint16_t*>(w->w_o), xs, T, hidden, (int64_t)Hq * D, kEpiAccumulate, split,
-                   split_bytes, s)) != TRAJ_OK)
+                   split_bytes, s, &pending)) != TRAJ_OK)
         return st;
     // MLP block
-    hipLaunchKernelGGL(rmsnorm_kernel, dim3((unsigned)T), dim3(kLayerThreads), 0, s, xs,
-                       static_cast<const uint16_t*>(w->mlp_norm), buf(plan.xn), hidden, dims->rms_eps);
-    if ((st = launched()) != TRAJ_OK) return st;
+    if ((st = rmsnorm(xs, w->mlp_norm, buf(plan.xn), T, hidden, dims->rms_eps, partial, pending, s)) != TRAJ_OK) return st;
     if ((st = gemm(buf(plan.xn), static_cast<const uint16_t*>(w->w_gate_up), buf(plan.act), T, 2 * (int64_t)inter, hidden,
                    kEpiSwiglu, split, split_bytes, s)) != TRAJ_OK)
         return st;

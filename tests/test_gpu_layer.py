@@ -55,6 +55,30 @@ def test_layer_parity(B, N, L, Hq, Hkv, D, S, inter, tree):
     assert float(err.mean()) < 2e-3 * rms, float(err.mean()) / rms
 
 
+@pytest.mark.parametrize("hidden,Hkv,D,inter,rows", [
+    # residual widths on either side of the norm's register-held row sizes (2048, 4096, 8192), few rows:
+    # the O projection is split and the second norm sums its partial products
+    (2048, 4, 64, 264, 5), (2176, 1, 128, 136, 33), (4224, 3, 128, 136, 5), (8192, 1, 128, 64, 3), (8256, 1, 64, 64, 5),
+])
+def test_layer_residual_widths(hidden, Hkv, D, inter, rows):
+    rng = np.random.default_rng(hidden)
+    Hq = hidden // D
+    x = bf16_round(rng.standard_normal((1, 1, rows, hidden)))
+    w = _weights(rng, hidden, Hq, Hkv, D, inter)
+    kc, vc = bf16_round(rng.standard_normal((1, 40, Hkv, D))), bf16_round(rng.standard_normal((1, 40, Hkv, D)))
+    parent = np.array([[-1]], dtype=np.int32)
+    ref = oracle.verify_layer(x, w, kc, vc, parent, Hq, pos0=np.array([17]), rms_eps=1e-5, rope_theta=500000.0)
+    bf = lambda a: cuda(np.asarray(a, dtype=np.float32), torch.bfloat16)  # noqa: E731
+    out = tsp.verify_layer(bf(x), {k: bf(v) for k, v in w.items()}, bf(kc), bf(vc), cuda(parent, torch.int32), Hq,
+                           pos0=cuda(np.array([17]), torch.int32))
+    g = out.float().cpu().numpy().astype(np.float64)
+    err, rms = np.abs(g - ref), math.sqrt(float(np.mean(ref * ref)))
+    assert (err <= 0.03 * np.abs(ref) + 0.03 * rms).all()
+    # few rows: results on both sides of a rounding boundary differ by one bf16 ulp (2^-8 relative), so
+    # the mean stays below one ulp of the rms even if every value were such a one
+    assert float(err.mean()) < 2.0 ** -8 * rms
+
+
 def test_layer_is_in_place_and_reports_bad_arguments():
     rng = np.random.default_rng(5)
     B, N, L, Hq, Hkv, D, S, inter = 1, 2, 4, 1, 1, 128, 16, 256
