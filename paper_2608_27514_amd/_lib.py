@@ -161,23 +161,28 @@ def _check(status, where):
 
 
 def _stream(stream):
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+    """The stream's handle.  The current one is asked for by handle: building a Stream object for it
+    takes 2.7 us, as long as the smallest kernels run."""
+    if stream is not None:
+        return stream.cuda_stream
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dev(t, name, dtype=None):
+    """Checks a device tensor argument; returns its address (None when it is empty)."""
     if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a CUDA (HIP) tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
     if dtype is not None and t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr() if t.numel() > 0 else None
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr() if t is not None and t.numel() > 0 else 0)
+    return t.data_ptr() if t is not None and t.numel() > 0 else None
 
 
 # ---------------------------------------------------------------- attention
@@ -196,27 +201,25 @@ def verify_attn(q, k_cache, v_cache, k_draft, v_draft, draft_parent, out=None, s
                 stream=None, peers=None):
     """Trajectory-masked attention; returns ``out`` [B,N,L,Hq,D] bf16.  ``peers`` ([B,N]
     int64 holding uint64 bit masks) adds visible drafts per draft (traj_verify_attn_peers)."""
-    for name, t in (("q", q), ("k_cache", k_cache), ("v_cache", v_cache), ("k_draft", k_draft),
-                    ("v_draft", v_draft)):
-        _dev(t, name, torch.bfloat16)
-    _dev(draft_parent, "draft_parent", torch.int32)
+    bf16 = torch.bfloat16
+    qp, kcp, vcp = _dev(q, "q", bf16), _dev(k_cache, "k_cache", bf16), _dev(v_cache, "v_cache", bf16)
+    kdp, vdp = _dev(k_draft, "k_draft", bf16), _dev(v_draft, "v_draft", bf16)
+    parent = _dev(draft_parent, "draft_parent", torch.int32)
     if peers is not None:
-        _dev(peers, "peers", torch.int64)
+        peers_p = _dev(peers, "peers", torch.int64)
         if tuple(peers.shape) != tuple(draft_parent.shape):
             raise ValueError("peers must be [B,N] like draft_parent")
     if out is None:
         out = torch.empty_like(q)
-    _dev(out, "out", torch.bfloat16)
+    outp = _dev(out, "out", bf16)
     shape = attn_shape(q, k_cache, scale)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     if peers is None:
-        st = _lib().traj_verify_attn(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(k_draft), _ptr(v_draft),
-                                     _ptr(draft_parent), _ptr(out), ctypes.byref(shape), _ptr(workspace),
+        st = _lib().traj_verify_attn(qp, kcp, vcp, kdp, vdp, parent, outp, ctypes.byref(shape), _ptr(workspace),
                                      ws_bytes, _stream(stream))
         _check(st, "traj_verify_attn")
     else:
-        st = _lib().traj_verify_attn_peers(_ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(k_draft), _ptr(v_draft),
-                                           _ptr(draft_parent), _ptr(peers), _ptr(out), ctypes.byref(shape),
+        st = _lib().traj_verify_attn_peers(qp, kcp, vcp, kdp, vdp, parent, peers_p, outp, ctypes.byref(shape),
                                            _ptr(workspace), ws_bytes, _stream(stream))
         _check(st, "traj_verify_attn_peers")
     return out
@@ -299,7 +302,7 @@ def confidence_topk(logits, k, conf=None, idx=None, workspace=None, stream=None)
         if need > 0:
             workspace = torch.empty(need, dtype=torch.uint8, device=logits.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = _lib().traj_confidence_topk(ctypes.c_void_p(logits.data_ptr()), int(k), _ptr(conf), _ptr(idx),
+    st = _lib().traj_confidence_topk(logits.data_ptr(), int(k), _ptr(conf), _ptr(idx),
                                      ctypes.byref(shape), _ptr(workspace), ws_bytes, _stream(stream))
     _check(st, "traj_confidence_topk")
     return conf, idx
@@ -320,7 +323,7 @@ def confidence_topk_noalloc(logits, k, conf=None, idx=None, stream=None):
         idx = torch.empty((R, k), dtype=torch.int32, device=logits.device)
     _dev(conf, "conf", torch.float32)
     _dev(idx, "idx", torch.int32)
-    st = _lib().traj_confidence_topk_noalloc(ctypes.c_void_p(logits.data_ptr()), int(k), _ptr(conf), _ptr(idx),
+    st = _lib().traj_confidence_topk_noalloc(logits.data_ptr(), int(k), _ptr(conf), _ptr(idx),
                                              ctypes.byref(shape), _stream(stream))
     _check(st, "traj_confidence_topk_noalloc")
     return conf, idx
@@ -336,24 +339,27 @@ def accept(conf, idx, tokens, parent, committed, conf0, idx0, threshold, mode="e
     k = conf0.shape[-1]
     if conf.numel() != B * N * L * k or idx.numel() != B * N * L * k:
         raise ValueError("conf/idx must hold B*N*L*k entries")
-    for name, t, dt in (("conf", conf, torch.float32), ("idx", idx, torch.int32), ("tokens", tokens, torch.int32),
-                        ("parent", parent, torch.int32), ("committed", committed, torch.int32),
-                        ("conf0", conf0, torch.float32), ("idx0", idx0, torch.int32)):
-        _dev(t, name, dt)
-    dev = tokens.device
+    f32, i32 = torch.float32, torch.int32
+    confp, idxp = _dev(conf, "conf", f32), _dev(idx, "idx", i32)
+    _dev(tokens, "tokens", i32)
+    _dev(parent, "parent", i32)
+    _dev(committed, "committed", i32)
+    _dev(conf0, "conf0", f32)
+    _dev(idx0, "idx0", i32)
     if out is None:
+        dev, empty = tokens.device, torch.empty
         out = {
-            "leaf": torch.empty(B, dtype=torch.int32, device=dev),
-            "on_path": torch.empty((B, N), dtype=torch.uint8, device=dev),
-            "n_accepted": torch.empty(B, dtype=torch.int32, device=dev),
-            "out_tokens": torch.empty((B, L), dtype=torch.int32, device=dev),
-            "hi": torch.empty((B, N, L), dtype=torch.uint8, device=dev),
+            "leaf": empty(B, dtype=i32, device=dev),
+            "on_path": empty((B, N), dtype=torch.uint8, device=dev),
+            "n_accepted": empty(B, dtype=i32, device=dev),
+            "out_tokens": empty((B, L), dtype=i32, device=dev),
+            "hi": empty((B, N, L), dtype=torch.uint8, device=dev),
         }
     dr = Drafts(B, N, L, k, tokens.data_ptr(), parent.data_ptr(), committed.data_ptr(), conf0.data_ptr(),
                 idx0.data_ptr(), MODES[mode], TRAVERSALS[traversal])
     ac = Accepted(out["leaf"].data_ptr(), out["on_path"].data_ptr(), out["n_accepted"].data_ptr(),
                   out["out_tokens"].data_ptr(), out["hi"].data_ptr())
-    st = _lib().traj_accept(_ptr(conf), _ptr(idx), ctypes.byref(dr), float(threshold), ctypes.byref(ac),
+    st = _lib().traj_accept(confp, idxp, ctypes.byref(dr), float(threshold), ctypes.byref(ac),
                             _stream(stream))
     _check(st, "traj_accept")
     return out
