@@ -84,6 +84,8 @@ constexpr int kAttnSplitKeysMin = 192;
 // over 2048 keys (28 x 4 heads) 39.8 -> 38.2 us, 32 x 32 over 1504 (32 heads) 36.3 -> 34.4, a
 // sequence of 768 over itself 43.7 -> 37.5; 512 keys 19.7 -> 19.6, 256 keys 15.6 -> 16.3.
 constexpr int kAttnSplitKeysMin32 = 512;
+// Weights per layer from which two layers displace a cache from the 256 MB last-level cache.
+constexpr int64_t kAttnWarmLayerBytes = 128ll << 20;
 
 // p describes the 32-row launch (4 waves x 32 rows per workgroup).  A grid that still has at
 // most one workgroup per CU with 16-row waves (4 waves x 16 rows per workgroup, twice the
@@ -108,6 +110,48 @@ traj_status launch_attn(AttnParams p, hipStream_t st) {
             hipLaunchKernelGGL((verify_attn_kernel<D, 1>), dim3(p.num_wg), dim3(kAttnThreads), 0, st, p);
     }
     return launched();
+}
+
+traj_status verify_attn(const void* q, const void* k_cache, const void* v_cache, const void* k_draft, const void* v_draft,
+                        const int32_t* draft_parent, const uint64_t* draft_peers, void* out, const traj_attn_shape* shape,
+                        bool warm, hipStream_t s) {
+    if (shape == nullptr || q == nullptr || k_draft == nullptr || v_draft == nullptr || draft_parent == nullptr ||
+        out == nullptr)
+        return TRAJ_E_NULL;
+    if (shape->S > 0 && (k_cache == nullptr || v_cache == nullptr)) return TRAJ_E_NULL;
+    traj_status st = check_attn(shape);
+    if (st != TRAJ_OK) return st;
+    if (!aligned16(q) || !aligned16(k_draft) || !aligned16(v_draft) || !aligned16(out) ||
+        (shape->S > 0 && (!aligned16(k_cache) || !aligned16(v_cache))))
+        return TRAJ_E_SHAPE;
+
+    AttnParams p{};
+    p.q = static_cast<const uint16_t*>(q);
+    p.kc = static_cast<const uint16_t*>(k_cache);
+    p.vc = static_cast<const uint16_t*>(v_cache);
+    p.kd = static_cast<const uint16_t*>(k_draft);
+    p.vd = static_cast<const uint16_t*>(v_draft);
+    p.parent = draft_parent;
+    p.peers = draft_peers;
+    p.out = static_cast<uint16_t*>(out);
+    p.B = shape->B;
+    p.N = shape->N;
+    p.L = shape->L;
+    p.Hq = shape->Hq;
+    p.Hkv = shape->Hkv;
+    p.S = shape->S;
+    p.group = shape->Hq / shape->Hkv;
+    p.rows_per_group = p.group * p.N * p.L;
+    const int rb = (p.rows_per_group + 31) / 32;
+    p.wg_per_group = (rb + kAttnWaves - 1) / kAttnWaves;
+    const int64_t nwg = (int64_t)p.B * p.Hkv * p.wg_per_group;
+    if (nwg > 0x7fffffff) return TRAJ_E_SHAPE;
+    p.num_wg = (int)nwg;
+    const float scale = shape->scale > 0.f ? shape->scale : 1.0f / std::sqrt((float)shape->D);
+    p.scale_log2 = scale * 1.4426950408889634f;
+    p.drafts_visible = 1;
+    p.warm = warm ? 1 : 0;
+    return shape->D == 128 ? launch_attn<128>(p, s) : launch_attn<64>(p, s);
 }
 
 // ------------------------------------------------------------------ confidence / top-k
@@ -481,43 +525,7 @@ traj_status traj_verify_attn_peers(const void* q, const void* k_cache, const voi
                                    void* stream) {
     (void)workspace;
     (void)workspace_bytes;
-    if (shape == nullptr || q == nullptr || k_draft == nullptr || v_draft == nullptr || draft_parent == nullptr ||
-        out == nullptr)
-        return TRAJ_E_NULL;
-    if (shape->S > 0 && (k_cache == nullptr || v_cache == nullptr)) return TRAJ_E_NULL;
-    traj_status st = check_attn(shape);
-    if (st != TRAJ_OK) return st;
-    if (!aligned16(q) || !aligned16(k_draft) || !aligned16(v_draft) || !aligned16(out) ||
-        (shape->S > 0 && (!aligned16(k_cache) || !aligned16(v_cache))))
-        return TRAJ_E_SHAPE;
-
-    AttnParams p{};
-    p.q = static_cast<const uint16_t*>(q);
-    p.kc = static_cast<const uint16_t*>(k_cache);
-    p.vc = static_cast<const uint16_t*>(v_cache);
-    p.kd = static_cast<const uint16_t*>(k_draft);
-    p.vd = static_cast<const uint16_t*>(v_draft);
-    p.parent = draft_parent;
-    p.peers = draft_peers;
-    p.out = static_cast<uint16_t*>(out);
-    p.B = shape->B;
-    p.N = shape->N;
-    p.L = shape->L;
-    p.Hq = shape->Hq;
-    p.Hkv = shape->Hkv;
-    p.S = shape->S;
-    p.group = shape->Hq / shape->Hkv;
-    p.rows_per_group = p.group * p.N * p.L;
-    const int rb = (p.rows_per_group + 31) / 32;
-    p.wg_per_group = (rb + kAttnWaves - 1) / kAttnWaves;
-    const int64_t nwg = (int64_t)p.B * p.Hkv * p.wg_per_group;
-    if (nwg > 0x7fffffff) return TRAJ_E_SHAPE;
-    p.num_wg = (int)nwg;
-    const float scale = shape->scale > 0.f ? shape->scale : 1.0f / std::sqrt((float)shape->D);
-    p.scale_log2 = scale * 1.4426950408889634f;
-    p.drafts_visible = 1;
-    hipStream_t s = as_stream(stream);
-    return shape->D == 128 ? launch_attn<128>(p, s) : launch_attn<64>(p, s);
+    return verify_attn(q, k_cache, v_cache, k_draft, v_draft, draft_parent, draft_peers, out, shape, false, as_stream(stream));
 }
 
 size_t traj_confidence_topk_workspace_size(const traj_logits_shape* shape, int32_t k) {
@@ -696,11 +704,17 @@ traj_status traj_verify_layer(void* x, const traj_layer_weights* w, const traj_l
     const LayerPlan plan = plan_layer(shape, dims);
     if (workspace_bytes < plan.total || reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return TRAJ_E_WORKSPACE;
     const int64_t T = (int64_t)shape->B * shape->N * shape->L;
+    // The cache was last read a forward pass ago: where the layers' weights since then have displaced it
+    // from the last-level cache it streams from HBM, and the attention's chain of steps waits for each
+    // stage unless the cache is read ahead (224 tokens, 736 keys: layer 195 -> 188 us; a cache that is
+    // still near costs the call 1 us more, 15.6 -> 16.7).
+    const bool warm = ((int64_t)dims->hidden * (shape->Hq + 2 * shape->Hkv + shape->Hq) * shape->D +
+                       3 * (int64_t)dims->hidden * dims->inter) * 2 >= kAttnWarmLayerBytes;
     // every draft's token p sits at position pos0[b] + p
     return run_layer(static_cast<uint16_t*>(x), w, dims, T, shape->Hq, shape->Hkv, shape->D, pos0,
                      shape->N * shape->L, shape->L, plan, static_cast<char*>(workspace), as_stream(stream),
                      [&](const uint16_t* q, const uint16_t* kd, const uint16_t* vd, uint16_t* a) {
-                         return traj_verify_attn(q, k_cache, v_cache, kd, vd, draft_parent, a, shape, nullptr, 0, stream);
+                         return verify_attn(q, k_cache, v_cache, kd, vd, draft_parent, nullptr, a, shape, warm, as_stream(stream));
                      });
 }
 

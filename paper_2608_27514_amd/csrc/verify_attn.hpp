@@ -74,6 +74,7 @@ struct AttnParams {
     int num_wg;
     float scale_log2;    // softmax scale * log2(e)
     int drafts_visible;  // 1: each draft sees its root path (+ peers); 0: queries see the cache only
+    int warm;            // 16-row kernel: read the cache into L2 ahead of the steps (it comes from HBM)
 };
 
 constexpr int kAttnWaves = 4;

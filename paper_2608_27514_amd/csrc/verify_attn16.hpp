@@ -36,6 +36,8 @@ namespace trajspec {
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
+constexpr int kAttnWarmLoads = 2;  // per wave: 128 lines, so 8 drafts' 32 waves cover 1024 keys of 128
+
 // Per-lane constants of the 16-row kernel.
 template <int D>
 struct AttnLane16 {
@@ -384,6 +386,26 @@ __global__ __launch_bounds__(kAttnThreads* KG, 2 / KG) void verify_attn16_kernel
             stage_dma<D, true, 16>(ca.krs, ca.vrs, kv_stride, 0, S, wave, ln, buf0);
         }
     }
+    // Warm the head's keys into this XCD's L2 (P.warm): a dword of each 128-byte line, the lines shared
+    // out over the waves of the head's workgroups, issued behind the first stage's loads.
+    uint32_t warm[kAttnWarmLoads] = {};
+    __builtin_amdgcn_sched_barrier(0);
+    if (P.warm) {
+        constexpr int LPR = D * 2 / 128;  // lines per key row
+        const int lines = P.S * LPR;  // K, and as many of V
+        const int waves = P.wg_per_group * kAttnWaves * KG, w = wg_in_group * kAttnWaves * KG + wave_all;
+        const uint16_t* kc0 = P.kc + ((int64_t)b * P.S * P.Hkv + g) * D;
+        const uint16_t* vc0 = P.vc + ((int64_t)b * P.S * P.Hkv + g) * D;
+#pragma unroll
+        for (int i = 0; i < kAttnWarmLoads; ++i) {
+            const int line = (i * waves + w) * 64 + lane;  // K lines, then V lines
+            if (line < 2 * lines) {
+                const int r = line < lines ? line : line - lines;
+                const int64_t at = (int64_t)(r / LPR) * kv_stride + (r % LPR) * 64;
+                warm[i] = *reinterpret_cast<const uint32_t*>((line < lines ? kc0 : vc0) + at);
+            }
+        }
+    }
     if (wave_all == 0) {
         uint64_t msk = 1ull << lane;
         int j = pj, prev = lane;
@@ -405,7 +427,10 @@ __global__ __launch_bounds__(kAttnThreads* KG, 2 / KG) void verify_attn16_kernel
         const uint64_t in_range = N == 64 ? ~0ull : ((1ull << N) - 1ull);
         if (lane < N) anc[lane] = P.drafts_visible ? (msk | (peer_bits & in_range)) : 0ull;
     }
-    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    if (P.warm)
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0 | kAttnWarmLoads);  // all but the warming loads, the last issued
+    else
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     __syncthreads();
     if (nb > 0) {
         qk16x4<D>(buf1, ln, qf, s);
@@ -493,6 +518,8 @@ __global__ __launch_bounds__(kAttnThreads* KG, 2 / KG) void verify_attn16_kernel
         }
     }
 
+#pragma unroll
+    for (int i = 0; i < kAttnWarmLoads; ++i) asm volatile("" ::"v"(warm[i]));  // keeps the warming loads
     // ---------------- epilogue ----------------
     const float l = quad_sum(st.lsum);
     const float inv = l > 0.f ? 1.0f / l : 0.f;
