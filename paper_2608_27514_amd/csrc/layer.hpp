@@ -1,15 +1,14 @@
 // One verification layer around the trajectory-masked attention (a pre-norm decoder layer of
 // the 8B-shaped diffusion LMs the method runs on): the elementwise kernels between the
-// library GEMMs (SwiGLU belongs to the
-// gate / up projection).  All activations are bf16 in HBM, arithmetic in fp32.
+// library GEMMs (SwiGLU belongs to the gate / up projection).  All activations are bf16 in HBM,
+// arithmetic in fp32.
 //   rmsnorm_kernel     out = x / sqrt(mean(x^2) + eps) * w            (one workgroup per token); after a
 //                      split projection it also adds the partial products to the residual stream
 //   rope_split_kernel  [q | k | v] rows of the QKV projection -> q, k_draft, v_draft in the
 //                      attention's layouts, rotary position embedding on q and k (pairs d and
 //                      d + D/2, angle = pos * theta^(-2d/D)); token p of every draft of a block
 //                      sits at position pos0[b] + p (the drafts are alternative states of the
-//                      same block)
-//   cache_gather_kernel  the dual-cache refresh's copy of the rotated K / V rows outside the
+//                      same block).  In the dual-cache refresh it also writes the rotated K / V rows outside the
 //                      current block into the prefix | suffix cache
 #pragma once
 
@@ -136,13 +135,22 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_kernel(uint16_t* __restrict__
 // every head then moves 16-byte chunks (8 elements of the first half and the matching 8 of the
 // second).  D % 16 == 0.  With SPLIT the rows are the sums of the projection's `splits` partial
 // products, rounded to bf16.  A thread's first chunks are requested before the angles are computed.
+// CacheRows: where the refresh also puts the K and V rows of the positions outside each sequence's block
+// [block_start[b], block_start[b] + L): [B, S, Hkv D], prefix rows then suffix rows (a block_start
+// outside [0, S] is reported and clamped).  kc == null: nowhere.
+struct CacheRows {
+    const int32_t* block_start;
+    uint16_t *kc, *vc;
+    int S, L;
+};
+
 template <bool SPLIT>
 __global__ __launch_bounds__(kLayerThreads) void rope_split_kernel(const uint16_t* __restrict__ qkv,
                                                                    const float* __restrict__ partial, int splits,
                                                                    const int32_t* __restrict__ pos0,
                                                                    uint16_t* __restrict__ q, uint16_t* __restrict__ kd,
                                                                    uint16_t* __restrict__ vd, int NL, int L, int Hq,
-                                                                   int Hkv, int D, float log2_theta) {
+                                                                   int Hkv, int D, float log2_theta, CacheRows cache) {
     __shared__ float cs[kLayerMaxHalf], sn[kLayerMaxHalf];
     const int t = blockIdx.x;
     const int b = t / NL;
@@ -177,6 +185,15 @@ __global__ __launch_bounds__(kLayerThreads) void rope_split_kernel(const uint16_
         const float inv_freq = exp2f(-(2.0f * d / (float)D) * log2_theta);
         sincosf((float)pos * inv_freq, &sn[d], &cs[d]);
     }
+    int64_t cache_row = -1;  // of this token, or none
+    if (cache.kc != nullptr) {
+        int bs = cache.block_start[b];
+        if (bs < 0 || bs > cache.S) {
+            if (p == 0 && blockIdx.y == 0 && threadIdx.x == 0) flag_device_status(4);
+            bs = bs < 0 ? 0 : cache.S;
+        }
+        if (p < bs || p >= bs + cache.L) cache_row = (int64_t)b * cache.S + (p < bs ? p : p - cache.L);
+    }
     __syncthreads();
     auto finish = [&](int i, const u32x4_t& a, const u32x4_t& c) {
         const int head = i / cpr, d0 = 8 * (i - head * cpr);
@@ -196,43 +213,18 @@ __global__ __launch_bounds__(kLayerThreads) void rope_split_kernel(const uint16_
                                           : vd + ((int64_t)t * Hkv + (head - Hq - Hkv)) * D;
         *reinterpret_cast<u32x4_t*>(dst + d0) = lo;
         *reinterpret_cast<u32x4_t*>(dst + d0 + half) = hi;
+        if (cache_row >= 0 && head >= Hq) {
+            const int kv = head - Hq;  // k heads, then v heads
+            uint16_t* c = (kv < Hkv ? cache.kc : cache.vc) + (cache_row * Hkv + (kv < Hkv ? kv : kv - Hkv)) * D;
+            *reinterpret_cast<u32x4_t*>(c + d0) = lo;
+            *reinterpret_cast<u32x4_t*>(c + d0 + half) = hi;
+        }
     };
     if (i0 < tasks) finish(i0, a0, c0);
     if (i1 < tasks) finish(i1, a1, c1);
     for (int i = first + 2 * stride; i < tasks; i += stride) {
         load(i, a0, c0);
         finish(i, a0, c0);
-    }
-}
-
-// Dual-cache refresh: the rotated K and V rows of every position outside the current block go
-// to the cache, prefix rows then suffix rows.  kd / vd: [B, T, Hkv D] (T = S + L positions);
-// caches: [B, S, Hkv D]; block_start[b] in [0, S] (a value outside is reported and clamped).
-// Grid-stride over the B * S * Hkv D / 8 chunks of 8 elements.
-__global__ __launch_bounds__(kLayerThreads) void cache_gather_kernel(const uint16_t* __restrict__ kd,
-                                                                     const uint16_t* __restrict__ vd,
-                                                                     const int32_t* __restrict__ block_start,
-                                                                     uint16_t* __restrict__ kc, uint16_t* __restrict__ vc,
-                                                                     int B, int S, int L, int width) {
-    const int cpr = width / 8;  // chunks per key row
-    const int64_t total = (int64_t)B * S * cpr;
-    const int T = S + L;
-    for (int64_t q = (int64_t)blockIdx.x * kLayerThreads + threadIdx.x; q < total;
-         q += (int64_t)gridDim.x * kLayerThreads) {
-        const int64_t row = q / cpr;  // b S + s
-        const int c = (int)(q - row * cpr);
-        const int b = (int)(row / S);
-        const int sp = (int)(row - (int64_t)b * S);
-        int bs = block_start[b];
-        if (bs < 0 || bs > S) {
-            if (sp == 0 && c == 0) flag_device_status(4);
-            bs = bs < 0 ? 0 : S;
-        }
-        const int t = sp < bs ? sp : sp + L;  // position in the sequence
-        const int64_t src = ((int64_t)b * T + t) * width + 8 * c;
-        const int64_t dst = row * width + 8 * c;
-        *reinterpret_cast<u32x4_t*>(kc + dst) = *reinterpret_cast<const u32x4_t*>(kd + src);
-        *reinterpret_cast<u32x4_t*>(vc + dst) = *reinterpret_cast<const u32x4_t*>(vd + src);
     }
 }
 

@@ -470,8 +470,8 @@ traj_status rmsnorm(uint16_t* x, const void* w, uint16_t* out, int64_t T, int hi
 // attention output a [T, Hq D].
 template <typename Attend>
 traj_status run_layer(uint16_t* xs, const traj_layer_weights* w, const traj_layer_dims* dims, int64_t T, int Hq,
-                      int Hkv, int D, const int32_t* pos0, int rope_nl, int rope_l, const LayerPlan& plan, char* ws,
-                      hipStream_t s, Attend attend) {
+                      int Hkv, int D, const int32_t* pos0, int rope_nl, int rope_l, const CacheRows& cache,
+                      const LayerPlan& plan, char* ws, hipStream_t s, Attend attend) {
     auto buf = [&](size_t off) { return reinterpret_cast<uint16_t*>(ws + off); };
     const int hidden = dims->hidden, inter = dims->inter;
     const int qkv_w = (Hq + 2 * Hkv) * D;
@@ -489,7 +489,7 @@ traj_status run_layer(uint16_t* xs, const traj_layer_weights* w, const traj_laye
     const unsigned rope_y = T < 1024 ? (unsigned)((qkv_w / 16 + kLayerThreads - 1) / kLayerThreads) : 1u;
     hipLaunchKernelGGL(pending > 1 ? rope_split_kernel<true> : rope_split_kernel<false>, dim3((unsigned)T, rope_y),
                        dim3(kLayerThreads), 0, s, buf(plan.qkv), partial, pending, pos0, buf(plan.q), buf(plan.kd),
-                       buf(plan.vd), rope_nl, rope_l, Hq, Hkv, D, std::log2(dims->rope_theta));
+                       buf(plan.vd), rope_nl, rope_l, Hq, Hkv, D, std::log2(dims->rope_theta), cache);
     if ((st = launched()) != TRAJ_OK) return st;
     if ((st = attend(buf(plan.q), buf(plan.kd), buf(plan.vd), buf(plan.a))) != TRAJ_OK) return st;
     if ((st = gemm(buf(plan.a), static_cast<const uint16_t*>(w->w_o), xs, T, hidden, (int64_t)Hq * D, kEpiAccumulate, split,
@@ -712,7 +712,7 @@ traj_status traj_verify_layer(void* x, const traj_layer_weights* w, const traj_l
                        3 * (int64_t)dims->hidden * dims->inter) * 2 >= kAttnWarmLayerBytes;
     // every draft's token p sits at position pos0[b] + p
     return run_layer(static_cast<uint16_t*>(x), w, dims, T, shape->Hq, shape->Hkv, shape->D, pos0,
-                     shape->N * shape->L, shape->L, plan, static_cast<char*>(workspace), as_stream(stream),
+                     shape->N * shape->L, shape->L, CacheRows{}, plan, static_cast<char*>(workspace), as_stream(stream),
                      [&](const uint16_t* q, const uint16_t* kd, const uint16_t* vd, uint16_t* a) {
                          return verify_attn(q, k_cache, v_cache, kd, vd, draft_parent, nullptr, a, shape, warm, as_stream(stream));
                      });
@@ -739,21 +739,13 @@ traj_status traj_refresh_layer(void* x, const traj_layer_weights* w, const traj_
     const int Tseq = shape->S + shape->L;
     const int64_t T = (int64_t)shape->B * Tseq;
     hipStream_t s = as_stream(stream);
-    // positions 0 .. T - 1 of each sequence; attention over the sequence's own K / V (the
-    // kernel's cache-only mode), after the rows outside the block have been copied to the cache
-    return run_layer(static_cast<uint16_t*>(x), w, dims, T, shape->Hq, shape->Hkv, shape->D, nullptr, Tseq, Tseq,
+    // positions 0 .. T - 1 of each sequence, the rows outside the block also to the cache; attention
+    // over the sequence's own K / V (the kernel's cache-only mode)
+    const CacheRows cache{block_start, shape->S > 0 ? static_cast<uint16_t*>(k_cache) : nullptr,
+                          static_cast<uint16_t*>(v_cache), shape->S, shape->L};
+    return run_layer(static_cast<uint16_t*>(x), w, dims, T, shape->Hq, shape->Hkv, shape->D, nullptr, Tseq, Tseq, cache,
                      plan, static_cast<char*>(workspace), s,
                      [&](const uint16_t* q, const uint16_t* kd, const uint16_t* vd, uint16_t* a) -> traj_status {
-                         if (shape->S > 0) {
-                             const int width = shape->Hkv * shape->D;
-                             const int64_t chunks = (int64_t)shape->B * shape->S * (width / 8);
-                             const unsigned grid = (unsigned)std::min<int64_t>((chunks + kLayerThreads - 1) / kLayerThreads, 8192);
-                             hipLaunchKernelGGL(cache_gather_kernel, dim3(grid), dim3(kLayerThreads), 0, s, kd, vd,
-                                                block_start, static_cast<uint16_t*>(k_cache),
-                                                static_cast<uint16_t*>(v_cache), shape->B, shape->S, shape->L, width);
-                             const traj_status gs = launched();
-                             if (gs != TRAJ_OK) return gs;
-                         }
                          return attn_cache_only(q, kd, vd, a, shape->B, Tseq, Tseq, shape->Hq, shape->Hkv, shape->D,
                                                 shape->scale, s);
                      });
