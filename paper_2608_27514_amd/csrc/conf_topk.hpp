@@ -538,10 +538,13 @@ struct TopkPlan {
 // per SIMD), 256 rows with 8 waves per row and 4-vector sweeps (2 waves per SIMD).  Fewer rows
 // than 128 run 8 waves per row and also split each row, so that the launch keeps about 128
 // workgroups.
+// Rows below kTopkShortRow values are over in a sweep or two: 4 waves instead of 8 to merge (400 rows
+// of 1000 fp32 6.9 -> 5.3 us, 32 rows of 2000 bf16 5.2 -> 5.0; 5001 values unchanged with 8).
+constexpr int64_t kTopkShortRow = 2048;
 inline TopkPlan plan_conf_topk(int64_t rows, int64_t vocab, int vec) {
     TopkPlan p{64, 2, 3, 1, (int)vocab};
     if (rows >= 4096) return p;
-    if (rows >= 512) return TopkPlan{256, 2, 2, 1, (int)vocab};
+    if (rows >= 512 || vocab < kTopkShortRow) return TopkPlan{256, 2, 2, 1, (int)vocab};
     if (rows >= 128) return TopkPlan{512, 4, 2, 1, (int)vocab};
     p = TopkPlan{512, 2, 2, 1, (int)vocab};
     const int64_t target = 128;
