@@ -334,9 +334,11 @@ traj_status traj_interblock_trigger(const int32_t* state, const float* conf, int
  *   w_qkv [hidden, (Hq + 2 Hkv) D]; w_o [Hq D, hidden]; w_gate_up [hidden, 2 inter] (gate then
  *   up); w_down [inter, hidden]; k_cache / v_cache and draft_parent as traj_verify_attn;
  *   pos0 [B] int32 (NULL = 0).  shape is the attention shape of the call (scale included).
- * workspace: at least traj_verify_layer_workspace_size() bytes, 256-byte aligned (the
- * intermediates: normed x, q/k/v, attention output, gate/up, activation; and the split-K
- * partial products of the projections for few-row shapes, as traj_linear).
+ * workspace: traj_verify_layer_workspace_size() bytes, 256-byte aligned (the intermediates:
+ * normed x, q/k/v, attention output, activation; and for few-row shapes the projections' scratch:
+ * split-K partial products as traj_linear, gate/up values).  One sized for a larger B N L of the same
+ * layer serves too, although its size may be the smaller one: the intermediates have to fit, the
+ * projections split as far as the rest allows.  TRAJ_E_WORKSPACE where the intermediates don't fit.
  * Limits: those of traj_verify_attn; hidden == Hq * D; hidden % 8 == 0; inter % 8 == 0.
  * ------------------------------------------------------------------------------------ */
 typedef struct {
@@ -373,7 +375,8 @@ traj_status traj_verify_layer(void* x, const traj_layer_weights* weights, const 
  * int32 device array in [0, S] (a value outside is clamped and sets TRAJ_DEV_BAD_BLOCK).
  * Weights, dims, rounding and limits as traj_verify_layer (shape->scale 0 = 1/sqrt(D)); one
  * sequence's T K / V rows must stay below 2 GiB.  x, the caches and the workspace must not overlap.
- * workspace: at least traj_refresh_layer_workspace_size() bytes, 256-byte aligned. */
+ * workspace: traj_refresh_layer_workspace_size() bytes, 256-byte aligned (or one of a larger
+ * B (S + L), as traj_verify_layer's). */
 typedef struct {
     int32_t B, S, L, Hq, Hkv, D;
     float scale;
@@ -397,8 +400,10 @@ traj_status traj_refresh_layer(void* x, const traj_layer_weights* weights, const
  * workspace (optional, may be NULL): shapes whose tiles leave CUs idle (few rows:
  * one or a few sequences' drafts) split K over several workgroups when given at least
  * traj_linear_workspace_size(M, K, N) bytes, 16-byte aligned, for the fp32 partial products
- * (a size of 0 means the shape is never split); with NULL the call runs unsplit.  A non-NULL
- * workspace that is too small or misaligned is TRAJ_E_WORKSPACE; it must not overlap x, w or y.
+ * (a size of 0 means the shape is not split); with NULL the call runs unsplit, with less it splits into
+ * fewer ranges.  A non-NULL workspace that is misaligned, or smaller than both that size and the partial
+ * products of min(256 / t, K / 512, 8) ranges (t = 128 x 128 tiles of y), is TRAJ_E_WORKSPACE; it must not
+ * overlap x, w or y.
  * Errors: TRAJ_E_SHAPE (sizes, alignment), TRAJ_E_UNSUPPORTED, TRAJ_E_NULL, TRAJ_E_WORKSPACE,
  * TRAJ_E_HIP (launch). */
 size_t traj_linear_workspace_size(int64_t M, int64_t K, int64_t N);

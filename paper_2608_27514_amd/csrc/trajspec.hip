@@ -264,12 +264,12 @@ struct GemmPlan {
     int splits, k_split;
 };
 
-// The tiling and K split with the least estimated time: rounds of workgroups over the CUs times
+// The tiling and K split (into at most max_splits ranges) with the least estimated time: rounds of workgroups over the CUs times
 // their steps, but at least the weights' streaming time, and for a split the second launch and its
 // partial products' traffic (written and read: 9 TB/s).  A split's reduction applies SwiGLU at no
 // cost; without one it is a launch of its own below kSwigluFuseMinRows.  Within a few percent of the
 // best measured tiling on 32 .. 2048 rows x the 8B projections.
-GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool swiglu, bool may_split) {
+GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool swiglu, int64_t max_splits) {
     GemmPlan best{};
     double best_us = 0.0;
     const int64_t steps = (K + kGemmBK - 1) / kGemmBK;
@@ -277,7 +277,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool swiglu, bool may_split)
         const int64_t tm = (M + g.bm - 1) / g.bm, tn = (N + g.bn - 1) / g.bn;
         const double stream_us = (double)K * (double)N * 2e-6 / g.stream;
         for (int s = 1; s <= kGemmMaxSplits; ++s) {
-            if (s > 1 && (!may_split || g.kernel[kEpiPartial] == nullptr || K / s < kGemmMinSplitK || tm * tn * s > kGemmCus)) break;
+            if (s > 1 && (s > max_splits || g.kernel[kEpiPartial] == nullptr || K / s < kGemmMinSplitK || tm * tn * s > kGemmCus)) break;
             const int64_t split_steps = (steps + s - 1) / s;
             if ((steps + split_steps - 1) / split_steps != s) continue;  // the same as a smaller s
             const double rounds = (double)((tm * tn * s + kGemmCus - 1) / kGemmCus);
@@ -295,25 +295,41 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool swiglu, bool may_split)
 
 bool gemm_sizes_ok(int64_t M, int64_t N, int64_t K) { return M >= 1 && N >= 8 && K >= 8 && K <= kGemmMaxK && N <= kGemmMaxN; }
 
+size_t partial_bytes(int64_t M, int64_t N) { return (size_t)M * (size_t)N * sizeof(float); }  // of one k range
+
 // fp32 partial products of a split GEMM (0 when the shape is not split)
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     if (!gemm_sizes_ok(M, N, K)) return 0;
-    const int splits = plan_gemm(M, N, K, false, true).splits;
-    return splits > 1 ? (size_t)splits * (size_t)M * (size_t)N * sizeof(float) : 0;
+    const int splits = plan_gemm(M, N, K, false, kGemmMaxSplits).splits;
+    return splits > 1 ? splits * partial_bytes(M, N) : 0;
+}
+
+// The least that traj_linear accepts as a workspace: the partial products of as many k ranges as 128 x 128
+// tiles leave CUs for, or of the plan where it takes fewer.  Fixed by the sizes, so that a workspace which
+// served a set of shapes goes on to serve them when the plan's figures change.
+size_t gemm_least_workspace_bytes(int64_t M, int64_t N, int64_t K) {
+    if (!gemm_sizes_ok(M, N, K)) return 0;
+    const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
+    int64_t splits = std::min<int64_t>(kGemmCus / tiles, std::min<int64_t>(K / kGemmMinSplitK, kGemmMaxSplits));
+    if (splits <= 1) return 0;
+    const int64_t steps = (K + kGemmBK - 1) / kGemmBK, split_steps = (steps + splits - 1) / splits;
+    splits = (steps + split_steps - 1) / split_steps;
+    return std::min(gemm_workspace_bytes(M, N, K), splits * partial_bytes(M, N));
 }
 
 // Scratch of the gate / up projection with SwiGLU: the partial products, or the [M, N] gate / up
 // values where SwiGLU is a launch of its own.
 size_t gemm_swiglu_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     if (!gemm_sizes_ok(M, N, K)) return 0;
-    const int splits = plan_gemm(M, N, K, true, true).splits;
-    if (splits > 1) return (size_t)splits * (size_t)M * (size_t)N * sizeof(float);
+    const int splits = plan_gemm(M, N, K, true, kGemmMaxSplits).splits;
+    if (splits > 1) return splits * partial_bytes(M, N);
     return M < kSwigluFuseMinRows ? (size_t)M * (size_t)N * sizeof(uint16_t) : 0;
 }
 
 // D[M,N] = A[M,K] W[K,N] (+ D with kEpiAccumulate), or with kEpiSwiglu D[M,N/2] = silu(gate) * up
 // of the product's [gate | up] columns; bf16 row-major, fp32 accumulation.  `ws` holds the split-K
-// partials (may be null or too small except for SwiGLU: the shape then runs unsplit).
+// partials: the plan splits into as many ranges as fit it (null: none), and SwiGLU stays in the epilogue
+// where the gate / up values don't fit.
 // With `pending` a split leaves its sum to the caller: *pending is the number of partial products in
 // ws (1: D holds the result).
 traj_status gemm(const uint16_t* A, const uint16_t* W, uint16_t* D, int64_t M, int64_t N, int64_t K, GemmEpilogue epi,
@@ -322,13 +338,11 @@ traj_status gemm(const uint16_t* A, const uint16_t* W, uint16_t* D, int64_t M, i
     if (M > INT_MAX - kG2BM) return TRAJ_E_SHAPE;
     if (K > kGemmMaxK || N > kGemmMaxN) return TRAJ_E_UNSUPPORTED;  // 32-bit buffer offsets
     if (!aligned16(A) || !aligned16(W) || !aligned16(D)) return TRAJ_E_SHAPE;
+    if (ws == nullptr || !aligned16(ws)) ws_bytes = 0;
     const bool swiglu = epi == kEpiSwiglu;
-    GemmPlan g = plan_gemm(M, N, K, swiglu, true);
-    if (g.splits > 1 &&
-        (ws == nullptr || ws_bytes < (size_t)g.splits * (size_t)M * (size_t)N * sizeof(float) || !aligned16(ws)))
-        g = plan_gemm(M, N, K, swiglu, false);
-    const bool apart = swiglu && g.splits == 1 && M < kSwigluFuseMinRows;  // SwiGLU as its own launch
-    if (apart && (ws == nullptr || ws_bytes < (size_t)M * (size_t)N * sizeof(uint16_t) || !aligned16(ws))) return TRAJ_E_WORKSPACE;
+    const GemmPlan g = plan_gemm(M, N, K, swiglu, (int64_t)(ws_bytes / partial_bytes(M, N)));
+    // SwiGLU as its own launch
+    const bool apart = swiglu && g.splits == 1 && M < kSwigluFuseMinRows && ws_bytes >= (size_t)M * (size_t)N * sizeof(uint16_t);
     const dim3 grid((unsigned)(g.tiles_m * g.tiles_n), (unsigned)g.splits);
     const GemmParams p{A, W, apart ? static_cast<uint16_t*>(ws) : D, (int)M, (int)N, (int)K, (int)g.tiles_m, (int)g.tiles_n,
                        g.splits > 1 ? static_cast<float*>(ws) : nullptr, g.k_split};
@@ -352,8 +366,10 @@ traj_status gemm(const uint16_t* A, const uint16_t* W, uint16_t* D, int64_t M, i
 
 size_t align256(size_t n) { return (n + 255) / 256 * 256; }
 
+// The intermediates' places in a layer's workspace.  What follows them is the projections' scratch: the
+// layer runs with any size of it (none: nothing is split), `total` holds what its plans would use.
 struct LayerPlan {
-    size_t xn, qkv, q, kd, vd, a, act, split, split_bytes, total;
+    size_t xn, qkv, q, kd, vd, a, act, split, total;
 };
 
 LayerPlan plan_layer(const traj_attn_shape* sh, const traj_layer_dims* dm) {
@@ -373,10 +389,10 @@ LayerPlan plan_layer(const traj_attn_shape* sh, const traj_layer_dims* dm) {
     p.a = take(T * (size_t)sh->Hq * sh->D * 2);
     p.act = take(T * (size_t)dm->inter * 2);
     const int64_t hid = dm->hidden, qkv_w = (int64_t)(sh->Hq + 2 * sh->Hkv) * sh->D;
-    p.split_bytes = std::max(std::max(gemm_workspace_bytes(T, qkv_w, hid), gemm_workspace_bytes(T, hid, (int64_t)sh->Hq * sh->D)),
-                             std::max(gemm_swiglu_workspace_bytes(T, 2 * (int64_t)dm->inter, hid),
-                                      gemm_workspace_bytes(T, hid, dm->inter)));
-    p.split = take(p.split_bytes);
+    const size_t scratch = std::max(std::max(gemm_workspace_bytes(T, qkv_w, hid), gemm_workspace_bytes(T, hid, (int64_t)sh->Hq * sh->D)),
+                                    std::max(gemm_swiglu_workspace_bytes(T, 2 * (int64_t)dm->inter, hid),
+                                             gemm_workspace_bytes(T, hid, dm->inter)));
+    p.split = take(scratch);
     p.total = off;
     return p;
 }
@@ -471,12 +487,12 @@ traj_status rmsnorm(uint16_t* x, const void* w, uint16_t* out, int64_t T, int hi
 template <typename Attend>
 traj_status run_layer(uint16_t* xs, const traj_layer_weights* w, const traj_layer_dims* dims, int64_t T, int Hq,
                       int Hkv, int D, const int32_t* pos0, int rope_nl, int rope_l, const CacheRows& cache,
-                      const LayerPlan& plan, char* ws, hipStream_t s, Attend attend) {
+                      const LayerPlan& plan, char* ws, size_t ws_bytes, hipStream_t s, Attend attend) {
     auto buf = [&](size_t off) { return reinterpret_cast<uint16_t*>(ws + off); };
     const int hidden = dims->hidden, inter = dims->inter;
     const int qkv_w = (Hq + 2 * Hkv) * D;
     void* split = ws + plan.split;
-    const size_t split_bytes = plan.split_bytes;
+    const size_t split_bytes = ws_bytes - plan.split;
     traj_status st;
     const float* partial = static_cast<const float*>(split);
     // attention block
@@ -702,7 +718,7 @@ traj_status traj_verify_layer(void* x, const traj_layer_weights* w, const traj_l
     if ((st = check_weights(x, w)) != TRAJ_OK) return st;
     if (shape->S > 0 && (k_cache == nullptr || v_cache == nullptr)) return TRAJ_E_NULL;
     const LayerPlan plan = plan_layer(shape, dims);
-    if (workspace_bytes < plan.total || reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return TRAJ_E_WORKSPACE;
+    if (workspace_bytes < plan.split || reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return TRAJ_E_WORKSPACE;
     const int64_t T = (int64_t)shape->B * shape->N * shape->L;
     // The cache was last read a forward pass ago: where the layers' weights since then have displaced it
     // from the last-level cache it streams from HBM, and the attention's chain of steps waits for each
@@ -712,7 +728,8 @@ traj_status traj_verify_layer(void* x, const traj_layer_weights* w, const traj_l
                        3 * (int64_t)dims->hidden * dims->inter) * 2 >= kAttnWarmLayerBytes;
     // every draft's token p sits at position pos0[b] + p
     return run_layer(static_cast<uint16_t*>(x), w, dims, T, shape->Hq, shape->Hkv, shape->D, pos0,
-                     shape->N * shape->L, shape->L, CacheRows{}, plan, static_cast<char*>(workspace), as_stream(stream),
+                     shape->N * shape->L, shape->L, CacheRows{}, plan, static_cast<char*>(workspace), workspace_bytes,
+                     as_stream(stream),
                      [&](const uint16_t* q, const uint16_t* kd, const uint16_t* vd, uint16_t* a) {
                          return verify_attn(q, k_cache, v_cache, kd, vd, draft_parent, nullptr, a, shape, warm, as_stream(stream));
                      });
@@ -735,7 +752,7 @@ traj_status traj_refresh_layer(void* x, const traj_layer_weights* w, const traj_
     if (shape->S > 0 && (k_cache == nullptr || v_cache == nullptr)) return TRAJ_E_NULL;
     if (shape->S > 0 && (!aligned16(k_cache) || !aligned16(v_cache))) return TRAJ_E_SHAPE;
     const LayerPlan plan = plan_layer(&as, dims);
-    if (workspace_bytes < plan.total || reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return TRAJ_E_WORKSPACE;
+    if (workspace_bytes < plan.split || reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return TRAJ_E_WORKSPACE;
     const int Tseq = shape->S + shape->L;
     const int64_t T = (int64_t)shape->B * Tseq;
     hipStream_t s = as_stream(stream);
@@ -744,7 +761,7 @@ traj_status traj_refresh_layer(void* x, const traj_layer_weights* w, const traj_
     const CacheRows cache{block_start, shape->S > 0 ? static_cast<uint16_t*>(k_cache) : nullptr,
                           static_cast<uint16_t*>(v_cache), shape->S, shape->L};
     return run_layer(static_cast<uint16_t*>(x), w, dims, T, shape->Hq, shape->Hkv, shape->D, nullptr, Tseq, Tseq, cache,
-                     plan, static_cast<char*>(workspace), s,
+                     plan, static_cast<char*>(workspace), workspace_bytes, s,
                      [&](const uint16_t* q, const uint16_t* kd, const uint16_t* vd, uint16_t* a) -> traj_status {
                          return attn_cache_only(q, kd, vd, a, shape->B, Tseq, Tseq, shape->Hq, shape->Hkv, shape->D,
                                                 shape->scale, s);
@@ -758,7 +775,7 @@ traj_status traj_linear(const void* x, const void* w, void* y, int64_t M, int64_
     if (M < 0 || K < 8 || N < 8 || K % 8 != 0 || N % 8 != 0) return TRAJ_E_SHAPE;
     if (M == 0) return TRAJ_OK;
     if (x == nullptr || w == nullptr || y == nullptr) return TRAJ_E_NULL;
-    if (workspace != nullptr && (workspace_bytes < gemm_workspace_bytes(M, N, K) || !aligned16(workspace)))
+    if (workspace != nullptr && (workspace_bytes < gemm_least_workspace_bytes(M, N, K) || !aligned16(workspace)))
         return TRAJ_E_WORKSPACE;
     return gemm(static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w), static_cast<uint16_t*>(y), M, N, K,
                 accumulate != 0 ? kEpiAccumulate : kEpiStore, workspace, workspace_bytes, as_stream(stream));

@@ -95,6 +95,75 @@ def test_layer_is_in_place_and_reports_bad_arguments():
         tsp.verify_layer(x, w, kc, vc, par, Hq, workspace=small)
 
 
+def _intermediates(T, Hq, Hkv, D, inter):
+    """What a layer's workspace has to hold: normed x, the QKV rows, q, k, v, the attention's output, the
+    activation, each rounded up to 256 bytes."""
+    cols = [Hq * D, (Hq + 2 * Hkv) * D, Hq * D, Hkv * D, Hkv * D, Hq * D, inter]
+    return sum(-(-2 * T * c // 256) * 256 for c in cols)
+
+
+@pytest.mark.parametrize("refresh", [False, True])
+def test_layer_workspace_of_a_larger_call(refresh):
+    """A workspace sized for the most tokens serves every smaller call of the layer, although the sizes do
+    not grow steadily with them (a K split of fewer rows takes more scratch), and so does one that holds the
+    intermediates alone (nothing split, SwiGLU in the projection's epilogue).  Outputs of the different
+    splits agree to the layer's compounded rounding, as in the parity tests."""
+    rng = np.random.default_rng(12)
+    Hq, Hkv, D, L, inter, S, most = 8, 4, 128, 32, 3072, 40, 20
+    hidden = Hq * D
+    bf = lambda a: cuda(np.asarray(a, dtype=np.float32), torch.bfloat16)  # noqa: E731
+    w = {k: bf(v) for k, v in _weights(rng, hidden, Hq, Hkv, D, inter).items()}
+
+    def run(n, ws):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(n)
+        x = torch.randn(1, n, L, hidden, device="cuda", generator=g).to(torch.bfloat16)
+        if refresh:  # n L tokens, the first L of them the block
+            x, kc, vc = tsp.refresh_layer(x.view(1, n * L, hidden), w, cuda(np.array([0]), torch.int32), Hq, Hkv, L,
+                                          workspace=ws)
+            return x.double(), kc.double(), vc.double()
+        kc, vc = (torch.randn(1, S, Hkv, D, device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+        parent = cuda(np.arange(n)[None] // 3 - 1, torch.int32)
+        return (tsp.verify_layer(x, w, kc, vc, parent, Hq, workspace=ws).double(),)
+
+    def size(n):
+        if refresh:
+            return tsp.refresh_layer_workspace_size(1, (n - 1) * L, L, Hq, Hkv, D, hidden, inter)
+        return tsp.layer_workspace_size(1, n, L, Hq, Hkv, D, S, hidden, inter)
+
+    large = torch.empty(size(most), dtype=torch.uint8, device="cuda")
+    least = torch.empty(_intermediates(most * L, Hq, Hkv, D, inter), dtype=torch.uint8, device="cuda")
+    for n in range(1, most + 1):
+        ref = run(n, torch.empty(size(n), dtype=torch.uint8, device="cuda"))
+        need = _intermediates(n * L, Hq, Hkv, D, inter)
+        for ws in (large, least[:need]):
+            for got, want in zip(run(n, ws), ref):
+                if want.numel() == 0:  # no cache
+                    continue
+                rms = want.square().mean().sqrt()
+                err = (got - want).abs()
+                assert (err <= 0.03 * want.abs() + 0.03 * rms).all(), n
+                assert err.mean() < 2.0 ** -8 * rms, n
+        with pytest.raises(tsp.TrajSpecError):
+            run(n, least[:need - 256])
+
+
+def test_linear_workspace_of_another_shape():
+    """A workspace that the K split of 128 x 128 tiles would fill (four ranges of 224 rows here) serves the
+    shape, whatever the plan takes by itself: it splits into as many ranges as fit."""
+    K, N = 12288, 4096
+    g = torch.Generator(device="cuda")
+    g.manual_seed(9)
+    w = (torch.randn(K, N, device="cuda", generator=g) * K ** -0.5).to(torch.bfloat16)
+    ws = torch.empty(4 * 224 * N * 4, dtype=torch.uint8, device="cuda")
+    for M in (224, 223, 200, 192, 160, 129):
+        x = torch.randn(M, K, device="cuda", generator=g).to(torch.bfloat16)
+        out = tsp.linear(x, w, workspace=ws)
+        x64, w64 = x.double(), w.double()
+        ref, mag = x64 @ w64, x64.abs() @ w64.abs()
+        assert ((out.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2.0 ** -15 * mag).all(), M
+
+
 # ---------------------------------------------------------------- the projection GEMM alone
 # The GPU accumulates bf16 products in fp32 (K / 16 dependent MFMA steps) and rounds once to
 # bf16; against the exact value: |gpu - ref| <= 2^-8 |ref| + 2^-15 (|x| @ |w| + |y0|).
