@@ -398,12 +398,12 @@ traj_status traj_refresh_layer(void* x, const traj_layer_weights* weights, const
  * 16-byte aligned; y must not overlap x or w.  The kernels address operands through 32-bit
  * buffer offsets: K <= 2^22 and N <= 2^24, else TRAJ_E_UNSUPPORTED.  Nothing is allocated.
  * workspace (optional, may be NULL): shapes whose tiles leave CUs idle (few rows:
- * one or a few sequences' drafts) split K over several workgroups when given at least
+ * one or a few sequences' drafts) split K over several workgroups when given
  * traj_linear_workspace_size(M, K, N) bytes, 16-byte aligned, for the fp32 partial products
  * (a size of 0 means the shape is not split); with NULL the call runs unsplit, with less it splits into
- * fewer ranges.  A non-NULL workspace that is misaligned, or smaller than both that size and the partial
- * products of min(256 / t, K / 512, 8) ranges (t = 128 x 128 tiles of y), is TRAJ_E_WORKSPACE; it must not
- * overlap x, w or y.
+ * fewer ranges.  A non-NULL workspace that is misaligned, or smaller than both what the shape's split takes
+ * and the partial products of min(256 / t, K / 512, 8) ranges (t = 128 x 128 tiles of y), is
+ * TRAJ_E_WORKSPACE; it must not overlap x, w or y.
  * Errors: TRAJ_E_SHAPE (sizes, alignment), TRAJ_E_UNSUPPORTED, TRAJ_E_NULL, TRAJ_E_WORKSPACE,
  * TRAJ_E_HIP (launch). */
 size_t traj_linear_workspace_size(int64_t M, int64_t K, int64_t N);

@@ -304,17 +304,17 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     return splits > 1 ? splits * partial_bytes(M, N) : 0;
 }
 
-// The least that traj_linear accepts as a workspace: the partial products of as many k ranges as 128 x 128
-// tiles leave CUs for, or of the plan where it takes fewer.  Fixed by the sizes, so that a workspace which
-// served a set of shapes goes on to serve them when the plan's figures change.
-size_t gemm_least_workspace_bytes(int64_t M, int64_t N, int64_t K) {
+// Partial products of as many k ranges as 128 x 128 tiles leave CUs for (0: none).  Fixed by the sizes: what
+// traj_linear reports is never below it and what it accepts never above, so that a workspace which served a
+// set of shapes goes on to serve them when the plan's figures change.
+size_t gemm_fixed_workspace_bytes(int64_t M, int64_t N, int64_t K) {
     if (!gemm_sizes_ok(M, N, K)) return 0;
     const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
     int64_t splits = std::min<int64_t>(kGemmCus / tiles, std::min<int64_t>(K / kGemmMinSplitK, kGemmMaxSplits));
     if (splits <= 1) return 0;
     const int64_t steps = (K + kGemmBK - 1) / kGemmBK, split_steps = (steps + splits - 1) / splits;
     splits = (steps + split_steps - 1) / split_steps;
-    return std::min(gemm_workspace_bytes(M, N, K), splits * partial_bytes(M, N));
+    return splits * partial_bytes(M, N);
 }
 
 // Scratch of the gate / up projection with SwiGLU: the partial products, or the [M, N] gate / up
@@ -768,15 +768,17 @@ traj_status traj_refresh_layer(void* x, const traj_layer_weights* w, const traj_
                      });
 }
 
-size_t traj_linear_workspace_size(int64_t M, int64_t K, int64_t N) { return gemm_workspace_bytes(M, N, K); }
+size_t traj_linear_workspace_size(int64_t M, int64_t K, int64_t N) {
+    return std::max(gemm_workspace_bytes(M, N, K), gemm_fixed_workspace_bytes(M, N, K));
+}
 
 traj_status traj_linear(const void* x, const void* w, void* y, int64_t M, int64_t K, int64_t N, int32_t accumulate,
                         void* workspace, size_t workspace_bytes, void* stream) {
     if (M < 0 || K < 8 || N < 8 || K % 8 != 0 || N % 8 != 0) return TRAJ_E_SHAPE;
     if (M == 0) return TRAJ_OK;
     if (x == nullptr || w == nullptr || y == nullptr) return TRAJ_E_NULL;
-    if (workspace != nullptr && (workspace_bytes < gemm_least_workspace_bytes(M, N, K) || !aligned16(workspace)))
-        return TRAJ_E_WORKSPACE;
+    const size_t least = std::min(gemm_workspace_bytes(M, N, K), gemm_fixed_workspace_bytes(M, N, K));
+    if (workspace != nullptr && (workspace_bytes < least || !aligned16(workspace))) return TRAJ_E_WORKSPACE;
     return gemm(static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w), static_cast<uint16_t*>(y), M, N, K,
                 accumulate != 0 ? kEpiAccumulate : kEpiStore, workspace, workspace_bytes, as_stream(stream));
 }

@@ -148,20 +148,28 @@ def test_layer_workspace_of_a_larger_call(refresh):
             run(n, least[:need - 256])
 
 
-def test_linear_workspace_of_another_shape():
-    """A workspace that the K split of 128 x 128 tiles would fill (four ranges of 224 rows here) serves the
-    shape, whatever the plan takes by itself: it splits into as many ranges as fit."""
-    K, N = 12288, 4096
+@pytest.mark.parametrize("K,N,most,smaller", [
+    (12288, 4096, 224, (223, 200, 192, 160, 129)),
+    # few rows: the larger call takes fewer ranges than the smaller ones
+    (4096, 4096, 65, (64, 48, 44)),
+    (12288, 4096, 65, (64, 53)),
+    (3584, 4608, 71, (70, 65)),
+])
+def test_linear_workspace_of_another_shape(K, N, most, smaller):
+    """A workspace of the size reported for more rows serves the shape, whatever the plan takes by itself: it
+    splits into as many ranges as fit.  So does one that the K split of 128 x 128 tiles would fill."""
     g = torch.Generator(device="cuda")
     g.manual_seed(9)
     w = (torch.randn(K, N, device="cuda", generator=g) * K ** -0.5).to(torch.bfloat16)
-    ws = torch.empty(4 * 224 * N * 4, dtype=torch.uint8, device="cuda")
-    for M in (224, 223, 200, 192, 160, 129):
-        x = torch.randn(M, K, device="cuda", generator=g).to(torch.bfloat16)
-        out = tsp.linear(x, w, workspace=ws)
-        x64, w64 = x.double(), w.double()
-        ref, mag = x64 @ w64, x64.abs() @ w64.abs()
-        assert ((out.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2.0 ** -15 * mag).all(), M
+    tiles = -(-most // 128) * -(-N // 128)
+    for size in (tsp.linear_workspace_size(most, K, N), min(256 // tiles, K // 512, 8) * most * N * 4):
+        ws = torch.empty(size, dtype=torch.uint8, device="cuda")
+        for M in (most, *smaller):
+            x = torch.randn(M, K, device="cuda", generator=g).to(torch.bfloat16)
+            out = tsp.linear(x, w, workspace=ws)
+            x64, w64 = x.double(), w.double()
+            ref, mag = x64 @ w64, x64.abs() @ w64.abs()
+            assert ((out.double() - ref).abs() <= 2.0 ** -8 * ref.abs() + 2.0 ** -15 * mag).all(), M
 
 
 # ---------------------------------------------------------------- the projection GEMM alone
