@@ -283,6 +283,12 @@ __device__ __forceinline__ void unpack(const u32x4_t& w, float (&x)[4]) {
 __device__ __forceinline__ float load_scalar(const uint16_t* p) { return bf16_bits_to_float(*p); }
 __device__ __forceinline__ float load_scalar(const float* p) { return *p; }
 
+// Unaligned rows of up to this many values per lane take scalar loads only: a vector sweep with its floor
+// and a scalar absorb behind it cost such a short row more than they save (bf16, 217 rows of 129 / 501 /
+// 1001 values: 3.5 / 3.9 / 4.6 us against 4.9 / 4.8 / 4.8; 1501: 5.3 against 4.8).  One wave per row (64
+// threads, thousands of rows) always gains by vectors (5000 rows of 129: 13.0 against 7.8).
+constexpr int kTopkScalarPerLane = 4;
+
 // grid.x = rows * splits; workgroup (row, split) covers [split * chunk, min(V, (split + 1) * chunk)).
 // Rows start at any element: the vectors are the 16-byte aligned ones inside the slice, and the up
 // to NV - 1 values before and after them go through one scalar absorb at the end (odd vocabularies:
@@ -326,7 +332,10 @@ __global__ __launch_bounds__(THREADS) void conf_topk_kernel(const T* __restrict_
         return fb;
     };
     // values before the first aligned vector
-    const int head = min((int)((0u - (unsigned)(reinterpret_cast<uintptr_t>(base + begin) / sizeof(T))) % NV), max(end - begin, 0));
+    const bool aligned = ((reinterpret_cast<uintptr_t>(logits) | (uint64_t)row_stride * sizeof(T)) & 15) == 0;  // every row
+    const bool scalar = THREADS == 256 && !aligned && end - begin <= kTopkScalarPerLane * THREADS;
+    const int lead = scalar ? end - begin : (int)((0u - (unsigned)(reinterpret_cast<uintptr_t>(base + begin) / sizeof(T))) % NV);
+    const int head = min(lead, max(end - begin, 0));
     const int vbegin = begin + head;
     const int nvec = (end - vbegin) / NV;
     {

@@ -130,9 +130,11 @@ def test_short_batch_launches_ragged_vocab(rows, V):
 
 # Rows that start anywhere inside a 16-byte vector: an odd stride moves the start from row to row
 # through every offset, under each launch shape (split rows, 8, 4 and 1 waves per row); V = 1 .. 5 is
-# shorter than the run up to the first aligned vector.
+# shorter than the run up to the first aligned vector; up to 1024 values workgroups of 4 waves read
+# one by one.
 @pytest.mark.parametrize("rows,V", [(40, 1), (40, 5), (40, 12301), (130, 16391), (130, 32999), (520, 4099),
-                                    (520, 20011), (4100, 1031), (4100, 9), (3, 126463)])
+                                    (520, 20011), (4100, 1031), (4100, 9), (3, 126463), (40, 257), (130, 1024),
+                                    (130, 1025), (520, 1023), (520, 1027), (4100, 1024)])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_rows_at_every_alignment(rows, V, dtype):
     rng = np.random.default_rng(rows + V)
