@@ -98,7 +98,7 @@ __device__ __forceinline__ gemm_i32x4_t gemm_descriptor(const void* base, unsign
 // saves it in a scratch SGPR and restores it after the load, so no code around it sees a
 // changed M0.  On gfx9 an SALU write of M0 needs one wait state before an LDS-DMA load reads
 // it (the compiler's hazard recognizer does not look inside asm), hence the s_nop.
-// NT: non-temporal, for an operand that no other workgroup reads.
+// NT: non-temporal, for an operand that few other workgroups read, and at about the same time.
 template <bool NT>
 __device__ __forceinline__ void gemm_dma16(const gemm_i32x4_t& rsrc, unsigned voffset, unsigned lds) {
     unsigned saved;

@@ -227,26 +227,34 @@ traj_status launch_topk(const void* logits, const traj_logits_shape* sh, int k, 
 struct GemmTiling {
     int bm, bn, threads;
     float step_us, stream, fill_us;
-    void (*kernel[4])(GemmParams);  // by GemmEpilogue
+    void (*kernel[2][4])(GemmParams);  // [at most two row tiles][GemmEpilogue]
 };
-#define TRAJ_RING_TILING(BM, BN, WM, WN, S, KC, NT, STEP, STREAM, FILL)                                             \
+// At most two row tiles share a W tile, at about the same time: the 64-row tilings then load W
+// non-temporally (gate / up of 64 / 96 / 128 rows 47.6 / 52.3 / 55.8 -> 46.5 / 51.0 / 54.7 us, down 33.7 / 36.5 /
+// 35.4 -> 32.9 / 36.2 / 35.0).  Where more share it the hint costs the others' reads (256 x 128 tiles with it
+// / without: 6100 x 2960 x 6760 308 / 250 us, 9904 x 728 x 6672 175 / 146).
+#define TRAJ_RING_KERNELS(BM, BN, WM, WN, S, KC, NT)                                                                \
+    {gemm_ring_kernel<BM, BN, WM, WN, S, KC, NT, kEpiStore>, gemm_ring_kernel<BM, BN, WM, WN, S, KC, NT, kEpiAccumulate>, \
+     gemm_ring_kernel<BM, BN, WM, WN, S, KC, NT, kEpiPartial>, gemm_ring_kernel<BM, BN, WM, WN, S, KC, NT, kEpiSwiglu>}
+#define TRAJ_RING_TILING(BM, BN, WM, WN, S, KC, STEP, STREAM, FILL)                                                 \
     {BM, BN, WM * WN * 64, STEP, STREAM, FILL,                                                                      \
-     {gemm_ring_kernel<BM, BN, WM, WN, S, KC, NT, kEpiStore>, gemm_ring_kernel<BM, BN, WM, WN, S, KC, NT, kEpiAccumulate>, \
-      gemm_ring_kernel<BM, BN, WM, WN, S, KC, NT, kEpiPartial>, gemm_ring_kernel<BM, BN, WM, WN, S, KC, NT, kEpiSwiglu>}}
+     {TRAJ_RING_KERNELS(BM, BN, WM, WN, S, KC, false), TRAJ_RING_KERNELS(BM, BN, WM, WN, S, KC, (BM == 64 && BN > 64))}}
 const GemmTiling kGemmTilings[] = {
-    TRAJ_RING_TILING(64, 64, 2, 2, 9, 4, false, 0.30f, 4.0f, 2.0f),
-    TRAJ_RING_TILING(64, 128, 2, 2, 3, 2, true, 0.42f, 5.5f, 4.0f),
-    TRAJ_RING_TILING(64, 256, 1, 4, 4, 1, true, 0.85f, 5.7f, 4.0f),
-    TRAJ_RING_TILING(128, 128, 2, 2, 4, 1, false, 0.55f, 5.0f, 4.0f),
-    TRAJ_RING_TILING(256, 96, 4, 1, 3, 1, false, 0.82f, 5.0f, 4.0f),
-    TRAJ_RING_TILING(256, 128, 4, 2, 3, 1, true, 0.90f, 5.4f, 4.0f),
-    TRAJ_RING_TILING(128, 192, 2, 2, 4, 1, false, 0.86f, 5.4f, 4.0f),
-    TRAJ_RING_TILING(192, 128, 2, 2, 4, 1, false, 0.74f, 5.0f, 4.0f),
-    TRAJ_RING_TILING(128, 256, 2, 4, 3, 1, false, 0.90f, 5.4f, 4.0f),
-    TRAJ_RING_TILING(192, 192, 2, 2, 3, 1, false, 1.03f, 5.4f, 4.0f),
+    TRAJ_RING_TILING(64, 64, 2, 2, 9, 4, 0.30f, 4.0f, 2.0f),
+    TRAJ_RING_TILING(64, 128, 2, 2, 3, 2, 0.42f, 5.5f, 4.0f),
+    TRAJ_RING_TILING(64, 256, 1, 4, 4, 1, 0.85f, 5.7f, 4.0f),
+    TRAJ_RING_TILING(128, 128, 2, 2, 4, 1, 0.55f, 5.0f, 4.0f),
+    TRAJ_RING_TILING(256, 96, 4, 1, 3, 1, 0.82f, 5.0f, 4.0f),
+    TRAJ_RING_TILING(256, 128, 4, 2, 3, 1, 0.90f, 5.4f, 4.0f),
+    TRAJ_RING_TILING(128, 192, 2, 2, 4, 1, 0.86f, 5.4f, 4.0f),
+    TRAJ_RING_TILING(192, 128, 2, 2, 4, 1, 0.74f, 5.0f, 4.0f),
+    TRAJ_RING_TILING(128, 256, 2, 4, 3, 1, 0.90f, 5.4f, 4.0f),
+    TRAJ_RING_TILING(192, 192, 2, 2, 3, 1, 1.03f, 5.4f, 4.0f),
     {kG2BM, kG2BN, kG2Threads, 1.62f, 5.4f, 4.0f,
-     {gemm_tile256_kernel<kEpiStore>, gemm_tile256_kernel<kEpiAccumulate>, nullptr, gemm_tile256_kernel<kEpiSwiglu>}},
+     {{gemm_tile256_kernel<kEpiStore>, gemm_tile256_kernel<kEpiAccumulate>, nullptr, gemm_tile256_kernel<kEpiSwiglu>},
+      {gemm_tile256_kernel<kEpiStore>, gemm_tile256_kernel<kEpiAccumulate>, nullptr, gemm_tile256_kernel<kEpiSwiglu>}}},
 };
+#undef TRAJ_RING_KERNELS
 #undef TRAJ_RING_TILING
 
 constexpr int kGemmCus = 256;           // workgroups the chip runs at a time
@@ -277,7 +285,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool swiglu, int64_t max_spl
         const int64_t tm = (M + g.bm - 1) / g.bm, tn = (N + g.bn - 1) / g.bn;
         const double stream_us = (double)K * (double)N * 2e-6 / g.stream;
         for (int s = 1; s <= kGemmMaxSplits; ++s) {
-            if (s > 1 && (s > max_splits || g.kernel[kEpiPartial] == nullptr || K / s < kGemmMinSplitK || tm * tn * s > kGemmCus)) break;
+            if (s > 1 && (s > max_splits || g.kernel[0][kEpiPartial] == nullptr || K / s < kGemmMinSplitK || tm * tn * s > kGemmCus)) break;
             const int64_t split_steps = (steps + s - 1) / s;
             if ((steps + split_steps - 1) / split_steps != s) continue;  // the same as a smaller s
             const double rounds = (double)((tm * tn * s + kGemmCus - 1) / kGemmCus);
@@ -346,7 +354,7 @@ traj_status gemm(const uint16_t* A, const uint16_t* W, uint16_t* D, int64_t M, i
     const dim3 grid((unsigned)(g.tiles_m * g.tiles_n), (unsigned)g.splits);
     const GemmParams p{A, W, apart ? static_cast<uint16_t*>(ws) : D, (int)M, (int)N, (int)K, (int)g.tiles_m, (int)g.tiles_n,
                        g.splits > 1 ? static_cast<float*>(ws) : nullptr, g.k_split};
-    hipLaunchKernelGGL(g.tiling->kernel[g.splits > 1 ? kEpiPartial : apart ? kEpiStore : epi], grid, dim3(g.tiling->threads), 0,
+    hipLaunchKernelGGL(g.tiling->kernel[g.tiles_m <= 2][g.splits > 1 ? kEpiPartial : apart ? kEpiStore : epi], grid, dim3(g.tiling->threads), 0,
                        st, p);
     const traj_status rs = launched();
     if (pending != nullptr) *pending = g.splits;
