@@ -222,11 +222,14 @@ traj_status launch_topk(const void* logits, const traj_logits_shape* sh, int k, 
 // the microseconds one 64-wide k step takes with a workgroup on every CU (one and two rounds of
 // 256 workgroups over K = 4096 and 12288), the rate in TB/s at which the weights stream when they
 // bound the call (wider tiles read longer row segments: LM head of 64 rows 240 / 194 / 176 us with
-// 64 / 128 / 256 columns), and the microseconds to fill and drain the stage ring.  Large tiles do
-// more arithmetic per step and byte, small ones fill the chip where M x N is small.
+// 64 / 128 / 256 columns), the microseconds to fill and drain the stage ring, and those that a further
+// round of workgroups takes beside its steps (its own fill and stores, fitted to K = 64 .. 512; the step
+// times, from kGemmLongSteps steps a round, hold them).  Without the last, short K ran on many rounds of
+// 64 x 64 tiles: 145 x 72 x 16832 13.0 us, 6.7 with it.  Large tiles do more arithmetic per step and byte,
+// small ones fill the chip where M x N is small.
 struct GemmTiling {
     int bm, bn, threads;
-    float step_us, stream, fill_us;
+    float step_us, stream, fill_us, round_us;
     void (*kernel[2][4])(GemmParams);  // [at most two row tiles][GemmEpilogue]
 };
 // At most two row tiles share a W tile, at about the same time: the 64-row tilings then load W
@@ -236,21 +239,21 @@ struct GemmTiling {
 #define TRAJ_RING_KERNELS(BM, BN, WM, WN, S, KC, NT)                                                                \
     {gemm_ring_kernel<BM, BN, WM, WN, S, KC, NT, kEpiStore>, gemm_ring_kernel<BM, BN, WM, WN, S, KC, NT, kEpiAccumulate>, \
      gemm_ring_kernel<BM, BN, WM, WN, S, KC, NT, kEpiPartial>, gemm_ring_kernel<BM, BN, WM, WN, S, KC, NT, kEpiSwiglu>}
-#define TRAJ_RING_TILING(BM, BN, WM, WN, S, KC, STEP, STREAM, FILL)                                                 \
-    {BM, BN, WM * WN * 64, STEP, STREAM, FILL,                                                                      \
+#define TRAJ_RING_TILING(BM, BN, WM, WN, S, KC, STEP, STREAM, FILL, ROUND)                                          \
+    {BM, BN, WM * WN * 64, STEP, STREAM, FILL, ROUND,                                                               \
      {TRAJ_RING_KERNELS(BM, BN, WM, WN, S, KC, false), TRAJ_RING_KERNELS(BM, BN, WM, WN, S, KC, (BM == 64 && BN > 64))}}
 const GemmTiling kGemmTilings[] = {
-    TRAJ_RING_TILING(64, 64, 2, 2, 9, 4, 0.30f, 4.0f, 2.0f),
-    TRAJ_RING_TILING(64, 128, 2, 2, 3, 2, 0.42f, 5.5f, 4.0f),
-    TRAJ_RING_TILING(64, 256, 1, 4, 4, 1, 0.85f, 5.7f, 4.0f),
-    TRAJ_RING_TILING(128, 128, 2, 2, 4, 1, 0.55f, 5.0f, 4.0f),
-    TRAJ_RING_TILING(256, 96, 4, 1, 3, 1, 0.82f, 5.0f, 4.0f),
-    TRAJ_RING_TILING(256, 128, 4, 2, 3, 1, 0.90f, 5.4f, 4.0f),
-    TRAJ_RING_TILING(128, 192, 2, 2, 4, 1, 0.86f, 5.4f, 4.0f),
-    TRAJ_RING_TILING(192, 128, 2, 2, 4, 1, 0.74f, 5.0f, 4.0f),
-    TRAJ_RING_TILING(128, 256, 2, 4, 3, 1, 0.90f, 5.4f, 4.0f),
-    TRAJ_RING_TILING(192, 192, 2, 2, 3, 1, 1.03f, 5.4f, 4.0f),
-    {kG2BM, kG2BN, kG2Threads, 1.62f, 5.4f, 4.0f,
+    TRAJ_RING_TILING(64, 64, 2, 2, 9, 4, 0.30f, 4.0f, 2.0f, 2.3f),
+    TRAJ_RING_TILING(64, 128, 2, 2, 3, 2, 0.42f, 5.5f, 4.0f, 1.7f),
+    TRAJ_RING_TILING(64, 256, 1, 4, 4, 1, 0.85f, 5.7f, 4.0f, 4.3f),
+    TRAJ_RING_TILING(128, 128, 2, 2, 4, 1, 0.55f, 5.0f, 4.0f, 3.3f),
+    TRAJ_RING_TILING(256, 96, 4, 1, 3, 1, 0.82f, 5.0f, 4.0f, 4.4f),
+    TRAJ_RING_TILING(256, 128, 4, 2, 3, 1, 0.90f, 5.4f, 4.0f, 5.0f),
+    TRAJ_RING_TILING(128, 192, 2, 2, 4, 1, 0.86f, 5.4f, 4.0f, 4.6f),
+    TRAJ_RING_TILING(192, 128, 2, 2, 4, 1, 0.74f, 5.0f, 4.0f, 4.7f),
+    TRAJ_RING_TILING(128, 256, 2, 4, 3, 1, 0.90f, 5.4f, 4.0f, 5.0f),
+    TRAJ_RING_TILING(192, 192, 2, 2, 3, 1, 1.03f, 5.4f, 4.0f, 6.3f),
+    {kG2BM, kG2BN, kG2Threads, 1.55f, 5.4f, 4.0f, 8.7f,
      {{gemm_tile256_kernel<kEpiStore>, gemm_tile256_kernel<kEpiAccumulate>, nullptr, gemm_tile256_kernel<kEpiSwiglu>},
       {gemm_tile256_kernel<kEpiStore>, gemm_tile256_kernel<kEpiAccumulate>, nullptr, gemm_tile256_kernel<kEpiSwiglu>}}},
 };
@@ -258,6 +261,7 @@ const GemmTiling kGemmTilings[] = {
 #undef TRAJ_RING_TILING
 
 constexpr int kGemmCus = 256;           // workgroups the chip runs at a time
+constexpr double kGemmLongSteps = 64.0;
 constexpr int64_t kGemmMinSplitK = 512;
 // SwiGLU goes into the GEMM's own epilogue from this many rows on: there the projection is bound
 // by the matrix cores and the gate / up values' round trip through memory costs as much as it
@@ -272,9 +276,9 @@ struct GemmPlan {
     int splits, k_split;
 };
 
-// The tiling and K split (into at most max_splits ranges) with the least estimated time: rounds of workgroups over the CUs times
-// their steps, but at least the weights' streaming time, and for a split the second launch and its
-// partial products' traffic (written and read: 9 TB/s).  A split's reduction applies SwiGLU at no
+// The tiling and K split (into at most max_splits ranges) with the least estimated time: rounds of
+// workgroups over the CUs times their steps, but at least the weights' streaming time, and for a split the
+// second launch and its partial products' traffic (written and read: 9 TB/s).  A split's reduction applies SwiGLU at no
 // cost; without one it is a launch of its own below kSwigluFuseMinRows.  Within a few percent of the
 // best measured tiling on 32 .. 2048 rows x the 8B projections.
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool swiglu, int64_t max_splits) {
@@ -289,7 +293,8 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool swiglu, int64_t max_spl
             const int64_t split_steps = (steps + s - 1) / s;
             if ((steps + split_steps - 1) / split_steps != s) continue;  // the same as a smaller s
             const double rounds = (double)((tm * tn * s + kGemmCus - 1) / kGemmCus);
-            double us = std::max(rounds * (double)split_steps * g.step_us, stream_us) + g.fill_us;
+            const double fills = (rounds - 1.0) * std::max(0.0, 1.0 - (double)split_steps / kGemmLongSteps) * g.round_us;
+            double us = std::max(rounds * (double)split_steps * g.step_us + fills, stream_us) + g.fill_us;
             if (s > 1) us += 2.0 + 0.4 * s + (double)s * (double)M * (double)N * 8.0 / 9e6;
             if (s == 1 && swiglu && M < kSwigluFuseMinRows) us += 6.0;
             if (best.tiling == nullptr || us < best_us) {
@@ -789,6 +794,15 @@ traj_status traj_linear(const void* x, const void* w, void* y, int64_t M, int64_
     if (workspace != nullptr && (workspace_bytes < least || !aligned16(workspace))) return TRAJ_E_WORKSPACE;
     return gemm(static_cast<const uint16_t*>(x), static_cast<const uint16_t*>(w), static_cast<uint16_t*>(y), M, N, K,
                 accumulate != 0 ? kEpiAccumulate : kEpiStore, workspace, workspace_bytes, as_stream(stream));
+}
+
+// For the tests: the plan of a product with all the workspace it asks for, as tile rows and columns and k
+// ranges.  Not part of the interface.
+void traj_test_gemm_plan(int64_t M, int64_t K, int64_t N, int32_t swiglu, int32_t plan[3]) {
+    const GemmPlan g = plan_gemm(M, N, K, swiglu != 0, kGemmMaxSplits);
+    plan[0] = g.tiling->bm;
+    plan[1] = g.tiling->bn;
+    plan[2] = g.splits;
 }
 
 const char* traj_status_string(int32_t status) {

@@ -263,6 +263,27 @@ def test_layer_and_linear_argument_errors():
     assert call(ws_bytes=16) == 5
 
 
+def gemm_plan(M, K, N, swiglu=False):
+    """(tile rows, tile columns, k ranges) that the library runs a product of these sizes with."""
+    out = (ctypes.c_int32 * 3)()
+    fn = _lib.load().traj_test_gemm_plan
+    fn.restype = None
+    fn.argtypes = [ctypes.c_int64, ctypes.c_int64, ctypes.c_int64, ctypes.c_int32, ctypes.POINTER(ctypes.c_int32)]
+    fn(M, K, N, 1 if swiglu else 0, out)
+    return tuple(out)
+
+
+@needs_lib
+@pytest.mark.parametrize("M,K,N", [(145, 72, 16832), (21, 336, 20240), (3, 240, 18192), (7188, 152, 6704), (5942, 168, 264)])
+def test_gemm_plan_of_few_k_steps_avoids_rounds_of_small_tiles(M, K, N):
+    """A round of workgroups costs its fill and stores beside its k steps; with few steps that is most of it,
+    so a product of more small tiles than the chip holds at a time takes larger ones."""
+    bm, bn, splits = gemm_plan(M, K, N)
+    assert splits == 1
+    tiles = -(-M // bm) * -(-N // bn)
+    assert tiles <= 256 or bm * bn == 256 * 256, (bm, bn)
+
+
 FLOOR_LIB = os.path.join(ROOT, "paper_2608_27514_amd", "libtrajfloor.so")
 
 
