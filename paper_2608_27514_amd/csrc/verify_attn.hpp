@@ -523,8 +523,10 @@ struct CacheArgs {
 // One 64-key step t of the cache phase whose next stage is full (64 t + 192 <= S): the softmax
 // phase turns the scores of blocks 2t, 2t+1 into weights; once every wave's loads of stage t have
 // landed (wait and barrier), the matrix phase computes the scores of blocks 2t+2, 2t+3, adds the
-// weighted V rows of blocks 2t, 2t+1 and issues the loads of stage t+1 between its MFMAs (issued
-// together before the softmax they held it up: the load path takes one per ~16 cycles and CU).
+// weighted V rows of blocks 2t, 2t+1 and issues the loads of stage t+1 between the first half of its MFMAs
+// (issued together before the softmax they held it up: the load path takes one per ~16 cycles and CU;
+// spread over all the MFMAs the last came too late for a cache in HBM: 16 sequences of 64 drafts x 32 over
+// 4096 keys 1969 us, 1932 so, 64 drafts of 4 sequences over 2048 keys 278 -> 275, of 11 x 8 over 3000 179 -> 173).
 // Two waves share each SIMD: one's softmax phase runs on the vector ALU while the other's matrix
 // phase runs on the matrix core.
 template <int D>
@@ -532,7 +534,7 @@ __device__ __forceinline__ void full_step(int t, const CacheArgs& a, const AttnL
                                           uint16_t* nxt, const bf16x8_t (&qf)[D / 16], f32x16_t (&s)[2], SoftState& st,
                                           f32x16_t (&o)[D / 32]) {
     using G = AttnGeom<D>;
-    constexpr int NM = 2 * (D / 16) + 4 * (D / 32), NL = 2 * G::kDmaPerWave;
+    constexpr int NM = D / 16 + 2 * (D / 32), NL = 2 * G::kDmaPerWave;  // MFMAs that loads follow, loads
     bf16x8_t pf[2][2];
     softmax_phase<D>(s, a.c, a.thr, st, o, pf);
     __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
@@ -542,7 +544,7 @@ __device__ __forceinline__ void full_step(int t, const CacheArgs& a, const AttnL
     // its softmax phase, the arbiter then keeps the matrix core fed first (-6% on 8b-batched)
     __builtin_amdgcn_s_setprio(1);
     matrix_pair<D>(cur, cur + G::kTileElems, ln, qf, s, pf, o, [&](int i) {
-        if ((i + 1) * NL / NM > i * NL / NM)
+        if (i < NM && (i + 1) * NL / NM > i * NL / NM)
             stage_dma_one<D>(a.krs, a.vrs, a.kv_stride, t + 1, a.S, a.wave, ln, nxt, i * NL / NM);
     });
     __builtin_amdgcn_sched_barrier(0);
