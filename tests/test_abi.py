@@ -7,6 +7,7 @@ import re
 
 import pytest
 
+from helpers import GEMM_ONE_PASS, GEMM_SPLIT, GEMM_SWIGLU
 from paper_2608_27514_amd import _lib
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -282,6 +283,19 @@ def test_gemm_plan_of_few_k_steps_avoids_rounds_of_small_tiles(M, K, N):
     assert splits == 1
     tiles = -(-M // bm) * -(-N // bn)
     assert tiles <= 256 or bm * bn == 256 * 256, (bm, bn)
+
+
+@needs_lib
+def test_gemm_plan_of_the_tested_shapes():
+    """The parity tests reach the tilings that they are there for."""
+    for (M, K, N), plan in {**GEMM_ONE_PASS, **GEMM_SPLIT}.items():
+        assert gemm_plan(M, K, N) == plan, (M, K, N)
+    for (drafts, tokens, hidden, inter), plan in GEMM_SWIGLU.items():
+        T = drafts * tokens
+        assert T >= 512 and T % plan[0] != 0 and inter % (plan[1] // 2) != 0
+        assert gemm_plan(T, hidden, 2 * inter, swiglu=True) == plan, (T, hidden, inter)
+    # the fused projection of a refresh of 768 tokens of the 8B layer
+    assert gemm_plan(768, 4096, 2 * 12288, swiglu=True) == (192, 192, 1)
 
 
 FLOOR_LIB = os.path.join(ROOT, "paper_2608_27514_amd", "libtrajfloor.so")

@@ -12,7 +12,7 @@ import torch
 
 import oracle
 import paper_2608_27514_amd as tsp
-from helpers import cuda
+from helpers import GEMM_ONE_PASS, GEMM_SPLIT, GEMM_SWIGLU, cuda
 from paper_2608_27514_amd import _lib
 from oracle.layer import bf16_round
 
@@ -53,6 +53,27 @@ def test_layer_parity(B, N, L, Hq, Hkv, D, S, inter, tree):
     rms = math.sqrt(float(np.mean(ref * ref)))
     assert (err <= 0.03 * np.abs(ref) + 0.03 * rms).all(), float((err - 0.03 * np.abs(ref) - 0.03 * rms).max())
     assert float(err.mean()) < 2e-3 * rms, float(err.mean()) / rms
+
+
+@pytest.mark.parametrize("N,L,hidden,inter", [*GEMM_SWIGLU])
+def test_layer_swiglu_each_tiling(N, L, hidden, inter):
+    """SwiGLU in the projection's epilogue: every tiling lays its gate and up columns out by itself.  The
+    activation's share of the output is large (a unit-variance MLP input), so a column out of place shows."""
+    rng = np.random.default_rng(N * L + inter)
+    D = 64
+    Hq = Hkv = hidden // D
+    x = bf16_round(rng.standard_normal((1, N, L, hidden)))
+    w = _weights(rng, hidden, Hq, Hkv, D, inter)
+    kc, vc = bf16_round(rng.standard_normal((1, 16, Hkv, D))), bf16_round(rng.standard_normal((1, 16, Hkv, D)))
+    parent = (np.arange(N, dtype=np.int32) // 3 - 1)[None]
+    ref = oracle.verify_layer(x, w, kc, vc, parent, Hq, pos0=np.array([5]), rms_eps=1e-5, rope_theta=500000.0)
+    bf = lambda a: cuda(np.asarray(a, dtype=np.float32), torch.bfloat16)  # noqa: E731
+    out = tsp.verify_layer(bf(x), {k: bf(v) for k, v in w.items()}, bf(kc), bf(vc), cuda(parent, torch.int32), Hq,
+                           pos0=cuda(np.array([5]), torch.int32))
+    g = out.float().cpu().numpy().astype(np.float64)
+    err, rms = np.abs(g - ref), math.sqrt(float(np.mean(ref * ref)))
+    assert (err <= 0.03 * np.abs(ref) + 0.03 * rms).all()
+    assert float(err.mean()) < 2e-3 * rms
 
 
 @pytest.mark.parametrize("hidden,Hkv,D,inter,rows", [
@@ -241,14 +262,7 @@ def test_linear_full_size_sampled_rows(M, K, N, acc):
     assert (np.abs(got - ref) <= _linear_bound(a_s, w_h, y_s, ref)).all()
 
 
-@pytest.mark.parametrize("M,K,N", [
-    # every tiling of the GEMM's plan, with ragged rows, columns and k: unsplit ...
-    (16, 200, 72), (66, 1096, 8216), (130, 328, 11120), (580, 200, 8312), (521, 200, 11232), (321, 200, 11240),
-    (643, 200, 10912), (385, 200, 11144), (769, 200, 6936), (968, 200, 11088), (64, 512, 33000),
-    # ... and split over k, the last range ragged
-    (16, 1544, 72), (68, 1544, 8296), (2053, 2056, 904), (261, 2056, 6616), (129, 2056, 5472), (4129, 2056, 392),
-    (193, 2056, 8344),
-])
+@pytest.mark.parametrize("M,K,N", [*GEMM_ONE_PASS, *GEMM_SPLIT])
 @pytest.mark.parametrize("acc", [False, True])
 def test_linear_each_tiling(M, K, N, acc):
     """Against the product in float64 with the bound above; the zeros past the last row, column and
