@@ -134,7 +134,7 @@ __global__ __launch_bounds__(THREADS) void rmsnorm_kernel(uint16_t* __restrict__
 // D / 2 rotation angles depend on the position only, so they are computed once per workgroup (into LDS);
 // every head then moves 16-byte chunks (8 elements of the first half and the matching 8 of the
 // second).  D % 16 == 0.  With SPLIT the rows are the sums of the projection's `splits` partial
-// products, rounded to bf16.  A thread's first chunks are requested before the angles are computed.
+// products, rounded to bf16.  A thread's first two pairs of chunks are requested before the angles are computed.
 // CacheRows: where the refresh also puts the K and V rows of the positions outside each sequence's block
 // [block_start[b], block_start[b] + L): [B, S, Hkv D], prefix rows then suffix rows (a block_start
 // outside [0, S] is reported and clamped).  kc == null: nowhere.
@@ -176,11 +176,11 @@ __global__ __launch_bounds__(kLayerThreads) void rope_split_kernel(const uint16_
         c = chunk(at + half);
     };
     const int pos = pos0 != nullptr ? pos0[b] + p : p;
-    u32x4_t a0, c0, a1, c1;
+    u32x4_t a0, c0, a1 = {}, c1 = {};
     const int first = blockIdx.y * kLayerThreads + threadIdx.x, stride = gridDim.y * kLayerThreads;
     const int i0 = first, i1 = first + stride;
     load(i0 < tasks ? i0 : 0, a0, c0);
-    load(i1 < tasks ? i1 : 0, a1, c1);
+    if (stride < tasks) load(i1 < tasks ? i1 : 0, a1, c1);  // uniform: a few tokens' threads have one pair
     for (int d = threadIdx.x; d < half; d += kLayerThreads) {
         const float inv_freq = exp2f(-(2.0f * d / (float)D) * log2_theta);
         sincosf((float)pos * inv_freq, &sn[d], &cs[d]);
