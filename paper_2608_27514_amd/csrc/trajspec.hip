@@ -219,14 +219,16 @@ traj_status launch_topk(const void* logits, const traj_logits_shape* sh, int k, 
 
 // ------------------------------------------------------------------ verification layer
 // Tilings of the projection GEMM with the figures its plan is made from, measured on an MI355X:
-// the microseconds one 64-wide k step takes with a workgroup on every CU (one and two rounds of
-// 256 workgroups over K = 4096 and 12288), the rate in TB/s at which the weights stream when they
-// bound the call (wider tiles read longer row segments: LM head of 64 rows 240 / 194 / 176 us with
-// 64 / 128 / 256 columns), the microseconds to fill and drain the stage ring, and those that a further
-// round of workgroups takes beside its steps (its own fill and stores, fitted to K = 64 .. 512; the step
-// times, from kGemmLongSteps steps a round, hold them).  Without the last, short K ran on many rounds of
-// 64 x 64 tiles: 145 x 72 x 16832 13.0 us, 6.7 with it.  Large tiles do more arithmetic per step and byte,
-// small ones fill the chip where M x N is small.
+// the microseconds one 64-wide k step takes with a workgroup on every CU, the rate in TB/s at which the
+// weights stream when they bound the call, the microseconds to fill and drain the stage ring, and those that
+// a further round of workgroups takes beside its steps (its own fill and stores, measured with K = 64 .. 512;
+// the step times, from kGemmLongSteps steps a round, hold them: without them 145 x 72 x 16832 ran on four
+// rounds of 64 x 64 tiles, 13.0 us against 6.7).  Large tiles do more arithmetic per step and byte, small ones
+// fill the chip where M x N is small.
+// The figures are those with which the plan comes nearest to the fastest tiling and split of 326 products of 1
+// .. 1024 rows (weights from HBM, every split; among them the projections and heads of 8B-class layers) and 180
+// products of 3 .. 32768 rows: 0.8% and 1.1% above it on the geometric mean, at worst 12% and 18%.  With earlier
+// figures, from one and two rounds of long K, few rows split too little: 128 x 12288 x 4096 34.0 us, 31.3 now.
 struct GemmTiling {
     int bm, bn, threads;
     float step_us, stream, fill_us, round_us;
@@ -243,17 +245,17 @@ struct GemmTiling {
     {BM, BN, WM * WN * 64, STEP, STREAM, FILL, ROUND,                                                               \
      {TRAJ_RING_KERNELS(BM, BN, WM, WN, S, KC, false), TRAJ_RING_KERNELS(BM, BN, WM, WN, S, KC, (BM == 64 && BN > 64))}}
 const GemmTiling kGemmTilings[] = {
-    TRAJ_RING_TILING(64, 64, 2, 2, 9, 4, 0.30f, 4.0f, 2.0f, 2.3f),
-    TRAJ_RING_TILING(64, 128, 2, 2, 3, 2, 0.42f, 5.5f, 4.0f, 1.7f),
-    TRAJ_RING_TILING(64, 256, 1, 4, 4, 1, 0.85f, 5.7f, 4.0f, 4.3f),
-    TRAJ_RING_TILING(128, 128, 2, 2, 4, 1, 0.55f, 5.0f, 4.0f, 3.3f),
-    TRAJ_RING_TILING(256, 96, 4, 1, 3, 1, 0.82f, 5.0f, 4.0f, 4.4f),
-    TRAJ_RING_TILING(256, 128, 4, 2, 3, 1, 0.90f, 5.4f, 4.0f, 5.0f),
-    TRAJ_RING_TILING(128, 192, 2, 2, 4, 1, 0.86f, 5.4f, 4.0f, 4.6f),
-    TRAJ_RING_TILING(192, 128, 2, 2, 4, 1, 0.74f, 5.0f, 4.0f, 4.7f),
-    TRAJ_RING_TILING(128, 256, 2, 4, 3, 1, 0.90f, 5.4f, 4.0f, 5.0f),
-    TRAJ_RING_TILING(192, 192, 2, 2, 3, 1, 1.03f, 5.4f, 4.0f, 6.3f),
-    {kG2BM, kG2BN, kG2Threads, 1.55f, 5.4f, 4.0f, 8.7f,
+    TRAJ_RING_TILING(64, 64, 2, 2, 9, 4, 0.34f, 4.1f, 3.5f, 2.3f),
+    TRAJ_RING_TILING(64, 128, 2, 2, 3, 2, 0.54f, 6.2f, 3.5f, 1.7f),
+    TRAJ_RING_TILING(64, 256, 1, 4, 4, 1, 0.97f, 6.6f, 4.0f, 4.3f),
+    TRAJ_RING_TILING(128, 128, 2, 2, 4, 1, 0.57f, 5.8f, 4.0f, 3.3f),
+    TRAJ_RING_TILING(256, 96, 4, 1, 3, 1, 0.755f, 5.4f, 4.0f, 4.4f),
+    TRAJ_RING_TILING(256, 128, 4, 2, 3, 1, 0.93f, 5.0f, 4.0f, 5.0f),
+    TRAJ_RING_TILING(128, 192, 2, 2, 4, 1, 0.855f, 5.4f, 4.0f, 4.6f),
+    TRAJ_RING_TILING(192, 128, 2, 2, 4, 1, 0.71f, 4.9f, 4.5f, 4.7f),
+    TRAJ_RING_TILING(128, 256, 2, 4, 3, 1, 0.92f, 6.6f, 5.0f, 5.0f),
+    TRAJ_RING_TILING(192, 192, 2, 2, 3, 1, 0.95f, 5.2f, 4.5f, 6.3f),
+    {kG2BM, kG2BN, kG2Threads, 1.40f, 5.5f, 3.5f, 8.7f,
      {{gemm_tile256_kernel<kEpiStore>, gemm_tile256_kernel<kEpiAccumulate>, nullptr, gemm_tile256_kernel<kEpiSwiglu>},
       {gemm_tile256_kernel<kEpiStore>, gemm_tile256_kernel<kEpiAccumulate>, nullptr, gemm_tile256_kernel<kEpiSwiglu>}}},
 };
@@ -278,9 +280,8 @@ struct GemmPlan {
 
 // The tiling and K split (into at most max_splits ranges) with the least estimated time: rounds of
 // workgroups over the CUs times their steps, but at least the weights' streaming time, and for a split the
-// second launch and its partial products' traffic (written and read: 9 TB/s).  A split's reduction applies SwiGLU at no
-// cost; without one it is a launch of its own below kSwigluFuseMinRows.  Within a few percent of the
-// best measured tiling on 32 .. 2048 rows x the 8B projections.
+// second launch and its partial products' traffic (written and read).  A split's reduction applies SwiGLU at no
+// cost; without one it is a launch of its own below kSwigluFuseMinRows.
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool swiglu, int64_t max_splits) {
     GemmPlan best{};
     double best_us = 0.0;
@@ -295,7 +296,7 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, bool swiglu, int64_t max_spl
             const double rounds = (double)((tm * tn * s + kGemmCus - 1) / kGemmCus);
             const double fills = (rounds - 1.0) * std::max(0.0, 1.0 - (double)split_steps / kGemmLongSteps) * g.round_us;
             double us = std::max(rounds * (double)split_steps * g.step_us + fills, stream_us) + g.fill_us;
-            if (s > 1) us += 2.0 + 0.4 * s + (double)s * (double)M * (double)N * 8.0 / 9e6;
+            if (s > 1) us += 3.2 + 0.27 * s + (double)s * (double)M * (double)N * 8.0 / 7.1e6;
             if (s == 1 && swiglu && M < kSwigluFuseMinRows) us += 6.0;
             if (best.tiling == nullptr || us < best_us) {
                 best = GemmPlan{&g, tm, tn, s, s > 1 ? (int)(split_steps * kGemmBK) : 0};

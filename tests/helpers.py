@@ -87,22 +87,24 @@ def compare_accept(gpu, ref, d, conf_ref, tau, B, N, L, k):
 # GEMM, ragged in rows, columns or k.  A change of the plan that moves one of them off its tiling has to
 # bring another shape for it.
 GEMM_ONE_PASS = {
-    (16, 200, 72): (64, 64, 1), (66, 1096, 8216): (64, 128, 1), (64, 512, 33000): (64, 256, 1),
-    (130, 328, 11120): (128, 128, 1), (580, 200, 8312): (128, 192, 1), (521, 200, 11232): (128, 256, 1),
-    (321, 200, 11240): (192, 128, 1), (643, 200, 10912): (192, 192, 1), (385, 200, 11144): (256, 96, 1),
-    (769, 200, 6936): (256, 128, 1), (968, 200, 11088): (256, 256, 1),
+    (16, 200, 72): (64, 64, 1), (66, 1096, 8216): (64, 128, 1), (9, 240, 43696): (64, 256, 1),
+    (130, 328, 11120): (128, 128, 1), (580, 200, 8312): (128, 192, 1), (2586, 160, 6080): (128, 256, 1),
+    (523, 160, 10184): (192, 128, 1), (643, 200, 10912): (192, 192, 1), (521, 200, 11232): (192, 192, 1),
+    (385, 200, 11144): (256, 96, 1), (321, 200, 11240): (256, 96, 1), (769, 200, 6936): (256, 128, 1),
+    (968, 200, 11088): (256, 256, 1), (64, 512, 33000): (128, 192, 1), (2053, 2056, 904): (128, 128, 1),
+    (261, 2056, 6616): (128, 128, 1), (193, 2056, 8344): (128, 128, 1),
 }
 GEMM_SPLIT = {
-    (16, 1544, 72): (64, 64, 3), (67, 3488, 2760): (64, 128, 5), (9, 2536, 7112): (64, 128, 3),
-    (9, 3056, 12992): (64, 256, 3), (68, 1544, 8296): (128, 128, 3), (2053, 2056, 904): (128, 192, 3),
-    (261, 2056, 6616): (128, 256, 3), (129, 2056, 5472): (192, 128, 4), (129, 2192, 10920): (192, 192, 4),
-    (4129, 2056, 392): (256, 96, 3), (193, 2056, 8344): (256, 128, 3),
+    (16, 1544, 72): (64, 64, 3), (67, 3488, 2760): (64, 128, 5), (9, 1632, 16520): (64, 256, 3),
+    (68, 1544, 8296): (128, 128, 3), (581, 2384, 3216): (128, 192, 3), (65, 2392, 16568): (128, 256, 3),
+    (130, 2160, 6184): (192, 128, 4), (130, 2456, 10968): (192, 192, 4), (129, 2056, 5472): (256, 96, 4),
+    (4129, 2056, 392): (256, 96, 3), (194, 2384, 8400): (256, 128, 3),
 }
 # Layers (drafts, tokens, hidden, inter) whose gate / up projection applies SwiGLU in its epilogue on each
 # tiling: rows not a multiple of the tile's, inter not one of its gate columns.
 GEMM_SWIGLU = {
     (40, 13, 192, 168): (64, 64, 1), (40, 13, 192, 904): (64, 128, 1), (34, 17, 192, 1616): (128, 128, 1),
-    (34, 17, 192, 4104): (128, 192, 1), (40, 13, 192, 5456): (128, 256, 1), (19, 27, 192, 3272): (192, 128, 1),
-    (19, 27, 192, 6544): (192, 192, 1), (42, 23, 192, 2696): (256, 96, 1), (15, 43, 192, 4104): (256, 128, 1),
+    (34, 17, 192, 4104): (128, 192, 1), (34, 17, 256, 6152): (128, 256, 1), (27, 19, 192, 4920): (192, 128, 1),
+    (19, 27, 192, 6544): (192, 192, 1), (19, 27, 192, 3272): (256, 96, 1), (15, 43, 192, 4104): (256, 128, 1),
     (34, 17, 192, 6568): (256, 256, 1),
 }
