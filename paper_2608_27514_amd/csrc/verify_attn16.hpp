@@ -36,7 +36,9 @@ namespace trajspec {
 
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kAttnWarmLoads = 2;  // per wave: 128 lines, so 8 drafts' 32 waves cover 1024 keys of 128
+// Warming loads per wave, 64 lines each: the 32 waves of 8 drafts of 32 tokens cover 1024 keys of 128 dims.  Fewer
+// waves or longer caches leave the last lines cold, V's first.
+constexpr int kAttnWarmLoads = 2;
 
 // Per-lane constants of the 16-row kernel.
 template <int D>
@@ -427,8 +429,12 @@ __global__ __launch_bounds__(kAttnThreads* KG, 2 / KG) void verify_attn16_kernel
         const uint64_t in_range = N == 64 ? ~0ull : ((1ull << N) - 1ull);
         if (lane < N) anc[lane] = P.drafts_visible ? (msk | (peer_bits & in_range)) : 0ull;
     }
+    // Only buf1's rows, older than every load of stage 0, have to be there (each step waits for everything
+    // before it reads its stage).  With the cache warmed the last kAttnWarmLoads loads stay in flight: the
+    // warming ones, or, in a wave whose lines all lie past the cache, loads of stage 0.
+    static_assert(2 * G::kDmaPerWave >= kAttnWarmLoads, "the loads left in flight are younger than buf1's");
     if (P.warm)
-        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0 | kAttnWarmLoads);  // all but the warming loads, the last issued
+        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0 | kAttnWarmLoads);
     else
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
     __syncthreads();

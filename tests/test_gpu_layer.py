@@ -100,6 +100,38 @@ def test_layer_residual_widths(hidden, Hkv, D, inter, rows):
     assert float(err.mean()) < 2.0 ** -8 * rms
 
 
+@pytest.fixture(scope="module")
+def wide_weights():
+    """A layer of 4096 x 4096 projections: with 128 MB of weights the attention reads the cache ahead."""
+    rng = np.random.default_rng(21)
+    hidden, inter = 4096, 64
+    f = lambda *s: bf16_round(rng.standard_normal(s, dtype=np.float32) / math.sqrt(s[0]))  # noqa: E731
+    w = {"attn_norm": bf16_round(1 + 0.1 * rng.standard_normal(hidden)), "w_qkv": f(hidden, 3 * hidden),
+         "w_o": f(hidden, hidden), "mlp_norm": bf16_round(1 + 0.1 * rng.standard_normal(hidden)),
+         "w_gate_up": f(hidden, 2 * inter), "w_down": f(inter, hidden)}
+    return w, {k: cuda(np.asarray(v, dtype=np.float32), torch.bfloat16) for k, v in w.items()}
+
+
+# one group of waves (up to 192 keys) and two; caches that end inside the first wave's lines, before the last
+# wave's, after all of them; no cache
+@pytest.mark.parametrize("D,S", [(128, 0), (128, 1), (128, 31), (128, 150), (128, 193), (128, 300), (64, 40), (64, 192),
+                                 (64, 450), (128, 1200)])
+def test_layer_with_the_cache_read_ahead(wide_weights, D, S):
+    w, wg = wide_weights
+    rng = np.random.default_rng(D + S)
+    H, N, L = 4096 // D, 3, 7
+    x = bf16_round(rng.standard_normal((1, N, L, 4096)))
+    kc, vc = bf16_round(rng.standard_normal((1, S, H, D))), bf16_round(rng.standard_normal((1, S, H, D)))
+    parent = np.array([[-1, 0, 0]], dtype=np.int32)
+    ref = oracle.verify_layer(x, w, kc, vc, parent, H, pos0=np.array([9]), rms_eps=1e-5, rope_theta=500000.0)
+    bf = lambda a: cuda(np.asarray(a, dtype=np.float32), torch.bfloat16)  # noqa: E731
+    out = tsp.verify_layer(bf(x), wg, bf(kc), bf(vc), cuda(parent, torch.int32), H, pos0=cuda(np.array([9]), torch.int32))
+    g = out.float().cpu().numpy().astype(np.float64)
+    err, rms = np.abs(g - ref), math.sqrt(float(np.mean(ref * ref)))
+    assert (err <= 0.03 * np.abs(ref) + 0.03 * rms).all()
+    assert float(err.mean()) < 2.0 ** -8 * rms
+
+
 def test_layer_is_in_place_and_reports_bad_arguments():
     rng = np.random.default_rng(5)
     B, N, L, Hq, Hkv, D, S, inter = 1, 2, 4, 1, 1, 128, 16, 256
