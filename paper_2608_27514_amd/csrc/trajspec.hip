@@ -474,7 +474,9 @@ traj_status attn_cache_only(const uint16_t* q, const uint16_t* k, const uint16_t
     return D == 128 ? launch_attn<128>(p, s) : launch_attn<64>(p, s);
 }
 
-// out = norm(x) * w over T rows; with splits > 1 x first gains the sum of the partial products.
+// out = norm(x) * w over T rows; with splits > 1 x first gains the sum of the partial products.  A launch
+// holds fewer than 2^32 threads, so more rows than kNormMaxRows take several (a split has far fewer).
+constexpr int64_t kNormMaxRows = (1ll << 32) / 512 - 1;
 template <bool SPLIT>
 traj_status launch_rmsnorm(uint16_t* x, const void* w, uint16_t* out, int64_t T, int hidden, float eps, const float* partial,
                            int splits, hipStream_t s) {
@@ -483,9 +485,14 @@ traj_status launch_rmsnorm(uint16_t* x, const void* w, uint16_t* out, int64_t T,
                   : nv <= 512  ? rmsnorm_kernel<512, 1, SPLIT>
                   : nv <= 1024 ? rmsnorm_kernel<512, 2, SPLIT>
                                : rmsnorm_kernel<512, 0, SPLIT>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)T), dim3(nv <= 256 ? 256 : 512), 0, s, x, static_cast<const uint16_t*>(w), out,
-                       hidden, eps, partial, splits);
-    return launched();
+    for (int64_t t = 0; t < T; t += kNormMaxRows) {
+        const dim3 grid((unsigned)std::min<int64_t>(T - t, kNormMaxRows));
+        hipLaunchKernelGGL(kernel, grid, dim3(nv <= 256 ? 256 : 512), 0, s, x + t * hidden, static_cast<const uint16_t*>(w),
+                           out + t * hidden, hidden, eps, partial, splits);
+        const traj_status st = launched();
+        if (st != TRAJ_OK) return st;
+    }
+    return TRAJ_OK;
 }
 
 traj_status rmsnorm(uint16_t* x, const void* w, uint16_t* out, int64_t T, int hidden, float eps, const float* partial, int splits,
