@@ -77,13 +77,14 @@ int device_cu_count() {
 }
 
 // 16-row grids with a longer cache than this run two key groups per workgroup (two waves per SIMD,
-// half the chain of steps each): 736 keys 16.9 -> 14.9 us, 4096 keys 54.5 -> 45.3 (8 drafts x 32
-// heads), 256 keys 10.6 -> 10.2; at 192 keys and below the merge costs what the steps save.
-constexpr int kAttnSplitKeysMin = 192;
-// The same for 32-row grids of at most one workgroup per CU, from this many keys on: 16 drafts of 64
-// over 2048 keys (28 x 4 heads) 39.8 -> 38.2 us, 32 x 32 over 1504 (32 heads) 36.3 -> 34.4, a
-// sequence of 768 over itself 43.7 -> 37.5; 512 keys 19.7 -> 19.6, 256 keys 15.6 -> 16.3.
-constexpr int kAttnSplitKeysMin32 = 512;
+// half the chain of steps each).  8 drafts x 32 heads x 128 dims, one group / two, cache from HBM and (near):
+// 256 keys 11.0 / 11.4 us (10.8 / 11.2), 384 14.1 / 14.2 (12.0 / 12.5), 448 15.5 / 15.1 (12.8 / 12.9), 736 21.2 /
+// 19.3 (16.7 / 15.9); up to 384 keys the merge costs what the steps save.
+constexpr int kAttnSplitKeysMin = 384;
+// The same for 32-row grids of at most one workgroup per CU, from this many keys on: 32 drafts x 32 heads over 512
+// keys 19.4 / 20.2 us (20.0 / 21.1), 768 24.2 / 24.1 (25.2 / 26.0), 1024 28.7 / 27.5 (29.2 / 29.4), 1504 38.2 / 35.9
+// (36.3 / 36.0); 16 drafts of 64 with 28 over 4 heads, 2048 keys 42.0 / 38.4 (39.6 / 38.9).
+constexpr int kAttnSplitKeysMin32 = 1024;
 // Weights per layer from which two layers displace a cache from the 256 MB last-level cache.
 constexpr int64_t kAttnWarmLayerBytes = 128ll << 20;
 

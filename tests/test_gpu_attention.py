@@ -117,10 +117,10 @@ def test_wrong_mask_is_detected(name):
     assert not ok
 
 
-# 16-row grids split their cache steps (64 keys) over two groups of waves from 193 keys on: either side
+# 16-row grids split their cache steps (64 keys) over two groups of waves from 385 keys on: either side
 # of that line, even and odd step counts, ragged last steps, and draft tiles shared out one by one
 # (L = 8: four drafts in a tile; L = 33: tiles mixing drafts).
-@pytest.mark.parametrize("S", [192, 193, 255, 256, 257, 320, 321, 705])
+@pytest.mark.parametrize("S", [192, 193, 255, 256, 257, 320, 321, 384, 385, 447, 448, 449, 512, 513, 705])
 @pytest.mark.parametrize("L,N,Hq,Hkv,D", [(8, 6, 4, 4, 64), (33, 4, 6, 2, 128)])
 @pytest.mark.parametrize("variant", ["spec", "sharp"])
 def test_key_groups(S, L, N, Hq, Hkv, D, variant):
@@ -134,8 +134,8 @@ def test_key_groups(S, L, N, Hq, Hkv, D, variant):
     assert ok, f"S={S}: worst excess {worst:.3g}, {frac:.2%} outside tolerance"
 
 
-# The same for 32-row grids of at most one workgroup per CU, from 512 keys on.
-@pytest.mark.parametrize("S", [511, 512, 513, 575, 640, 641, 833])
+# The same for 32-row grids of at most one workgroup per CU, from 1024 keys on.
+@pytest.mark.parametrize("S", [511, 512, 513, 575, 640, 641, 833, 1023, 1024, 1025, 1087, 1152, 1153, 1345])
 @pytest.mark.parametrize("L,N,Hq,Hkv,D", [(8, 16, 4, 4, 64), (33, 4, 6, 2, 128)])
 def test_key_groups_of_32_rows(S, L, N, Hq, Hkv, D):
     wl = Workload(99, "groups", B=2, N=N, L=L, Hq=Hq, Hkv=Hkv, D=D, S_prefix=S, S_suffix=0, V=64,

@@ -112,10 +112,10 @@ def wide_weights():
     return w, {k: cuda(np.asarray(v, dtype=np.float32), torch.bfloat16) for k, v in w.items()}
 
 
-# one group of waves (up to 192 keys) and two; caches that end inside the first wave's lines, before the last
+# one group of waves (up to 384 keys) and two; caches that end inside the first wave's lines, before the last
 # wave's, after all of them; no cache
-@pytest.mark.parametrize("D,S", [(128, 0), (128, 1), (128, 31), (128, 150), (128, 193), (128, 300), (64, 40), (64, 192),
-                                 (64, 450), (128, 1200)])
+@pytest.mark.parametrize("D,S", [(128, 0), (128, 1), (128, 31), (128, 150), (128, 193), (128, 384), (128, 385), (128, 700),
+                                 (64, 40), (64, 192), (64, 384), (64, 450), (128, 1200)])
 def test_layer_with_the_cache_read_ahead(wide_weights, D, S):
     w, wg = wide_weights
     rng = np.random.default_rng(D + S)
