@@ -2,7 +2,7 @@
 // row-major bf16, fp32 accumulation on v_mfma_f32_32x32x16_bf16, one bf16 rounding (nearest
 // even) of each result.  A holds the packed draft tokens (M = B N L rows), W a weight matrix.
 //
-// Tilings: gemm_ring_kernel (64 x 64 .. 192 x 192 tiles) and gemm_tile256_kernel (256 x 256), chosen
+// Tilings: gemm_ring_kernel (64 x 64 .. 256 x 128 tiles) and gemm_tile256_kernel (256 x 256), chosen
 // by the host from the sizes.
 //
 // Fragments: the MFMA takes 8 k-values per lane; lane half h = lane / 32 holds k = 8h .. 8h+7
@@ -547,9 +547,9 @@ __global__ __launch_bounds__(256) void swiglu_kernel(const uint16_t* __restrict_
 //   * Fragments are read one 16-wide k slice ahead, one after each MFMA.  The workgroup meets between
 //     the two slices of half step h: there every wave has read all of W half-stage h (and, for odd h,
 //     of its A stage) and has waited for its loads of half-stage h + 1.
-// Measured at 32768 x 4096 x 12288 (random bf16): 2690 -> 2520 us (1.22 -> 1.31 PFLOP/s); busy cycles
-// per launch 4.9 -> 4.3 million per XCD (MFMA busy 64 -> 74%), at a clock that falls from 1.83 to 1.7
-// GHz with the higher power.
+// Measured at 32768 x 4096 x 12288 (random bf16), against two 64 KB stages loaded at the start of a step:
+// 2825 -> 2650 us (1.17 -> 1.24 PFLOP/s), timed in turn; cycles per launch 4.93 -> 4.27 million per XCD (MFMA busy
+// 63.8 -> 73.7%), at a clock that falls from 1.69 to 1.49 GHz under the counters.
 constexpr int kG2BM = 256;
 constexpr int kG2BN = 256;
 constexpr int kG2BK = 64;                              // k per A stage; a W half-stage holds 32

@@ -87,6 +87,11 @@ constexpr int kAttnSplitKeysMin = 384;
 constexpr int kAttnSplitKeysMin32 = 1024;
 // Weights per layer from which two layers displace a cache from the 256 MB last-level cache.
 constexpr int64_t kAttnWarmLayerBytes = 128ll << 20;
+// 16-row workgroups per kv head from which the cache is read ahead: each of them streams the whole head, and
+// the read-ahead shares its first pass out between them.  Layers without / with it: 1 and 4 drafts of 32 heads (1
+// and 2 workgroups), 736 keys 127.2 / 128.6 and 168.4 / 169.8 us, 5 drafts (3) 193.6 / 193.6, 7 drafts (4) 197.0 / 196.2,
+// over 2048 keys 215.6 / 212.9; 32 over 8 heads, 2048 keys, 1 / 4 drafts (2 / 8) 135.5 / 136.7 and 180.2 / 172.8.
+constexpr int kAttnWarmMinWorkgroups = 4;
 
 // p describes the 32-row launch (4 waves x 32 rows per workgroup).  A grid that still has at
 // most one workgroup per CU with 16-row waves (4 waves x 16 rows per workgroup, twice the
@@ -100,6 +105,7 @@ traj_status launch_attn(AttnParams p, hipStream_t st) {
     if (nwg16 <= device_cu_count()) {
         p.wg_per_group = wg16;
         p.num_wg = (int)nwg16;
+        if (wg16 < kAttnWarmMinWorkgroups) p.warm = 0;
         if (p.S > kAttnSplitKeysMin)
             hipLaunchKernelGGL((verify_attn16_kernel<D, 2>), dim3(p.num_wg), dim3(2 * kAttnThreads), 0, st, p);
         else
@@ -744,8 +750,7 @@ traj_status traj_verify_layer(void* x, const traj_layer_weights* w, const traj_l
     const int64_t T = (int64_t)shape->B * shape->N * shape->L;
     // The cache was last read a forward pass ago: where the layers' weights since then have displaced it
     // from the last-level cache it streams from HBM, and the attention's chain of steps waits for each
-    // stage unless the cache is read ahead (224 tokens, 736 keys: layer 195 -> 188 us; a cache that is
-    // still near costs the call 1 us more, 15.6 -> 16.7).
+    // stage unless the cache is read ahead (a cache that is still near costs the call 1 us more).
     const bool warm = ((int64_t)dims->hidden * (shape->Hq + 2 * shape->Hkv + shape->Hq) * shape->D +
                        3 * (int64_t)dims->hidden * dims->inter) * 2 >= kAttnWarmLayerBytes;
     // every draft's token p sits at position pos0[b] + p

@@ -119,7 +119,7 @@ def wide_weights():
 def test_layer_with_the_cache_read_ahead(wide_weights, D, S):
     w, wg = wide_weights
     rng = np.random.default_rng(D + S)
-    H, N, L = 4096 // D, 3, 7
+    H, N, L = 4096 // D, 3, 67  # 201 rows: four workgroups of 64 rows per head, the fewest that read ahead
     x = bf16_round(rng.standard_normal((1, N, L, 4096)))
     kc, vc = bf16_round(rng.standard_normal((1, S, H, D))), bf16_round(rng.standard_normal((1, S, H, D)))
     parent = np.array([[-1, 0, 0]], dtype=np.int32)
