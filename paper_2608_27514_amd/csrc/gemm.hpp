@@ -548,8 +548,8 @@ __global__ __launch_bounds__(256) void swiglu_kernel(const uint16_t* __restrict_
 //     the two slices of half step h: there every wave has read all of W half-stage h (and, for odd h,
 //     of its A stage) and has waited for its loads of half-stage h + 1.
 // Measured at 32768 x 4096 x 12288 (random bf16), against two 64 KB stages loaded at the start of a step:
-// 2825 -> 2650 us (1.17 -> 1.24 PFLOP/s), timed in turn; cycles per launch 4.93 -> 4.27 million per XCD (MFMA busy
-// 63.8 -> 73.7%), at a clock that falls from 1.69 to 1.49 GHz under the counters.
+// 2825 -> 2650 us (1.17 -> 1.24 PFLOP/s), timed in turn; cycles per launch 5.03 -> 4.26 million per XCD (MFMA busy
+// 62.6 -> 73.8%), at a clock that falls from 1.81 to 1.60 GHz.
 constexpr int kG2BM = 256;
 constexpr int kG2BN = 256;
 constexpr int kG2BK = 64;                              // k per A stage; a W half-stage holds 32
